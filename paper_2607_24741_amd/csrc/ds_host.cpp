@@ -107,6 +107,9 @@ ds::Layout plan(const ds_problem* pr, const ds_options* op, void* ws) {
   L.es = uses_f64(pr, op) ? 2 : 1;
   if (L.mat) L.dp = 0;   // no point records: the cost is materialised
   L.rbmax = std::max(L.pad[0], L.pad[1]) / L.rows;
+  const int aunit = L.es == 2 && !(op->flags & DS_F_GUARD) ? ds::kRowsDig : L.rows;
+  while ((1 << L.ashift) < aunit) L.ashift++;   // (a power of two)
+  L.abmax = std::max(L.pad[0], L.pad[1]) / aunit;
   const size_t W = (size_t)pr->W;
   Carver c{reinterpret_cast<char*>(ws)};
   for (int b = 0; b < 2; ++b) {
@@ -123,7 +126,7 @@ ds::Layout plan(const ds_problem* pr, const ds_options* op, void* ws) {
     B.slot = c.take<ds::SlotInfo>(W);
     for (int role = 0; role < 2; ++role) B.ord[role] = c.take<int>(W);
     B.dec = c.take<ds::Decision>(W);
-    for (int k = 0; k < 4; ++k) B.agg[k] = c.take<float4>(W * (size_t)L.rbmax);
+    for (int k = 0; k < 4; ++k) B.agg[k] = c.take<float4>(W * (size_t)L.abmax);
   }
   L.center = c.take<float>(W * (size_t)L.d);
   L.vcnt = c.take<int>(W);
@@ -349,8 +352,11 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
   ia.pad[0] = L.pad[0]; ia.pad[1] = L.pad[1];
   ia.bank = L.bank[0];
   ia.center = L.center;
-  ia.vcnt = L.vcnt; ia.nchk = L.nchk; ia.disc = L.disc; ia.row64 = L.row64; ia.rbmax = L.rbmax;
+  ia.vcnt = L.vcnt; ia.nchk = L.nchk; ia.disc = L.disc; ia.row64 = L.row64; ia.abmax = L.abmax;
   ia.precise = precise ? 1 : 0;
+  // (guarded release keeps the doubles: its outward bound and its certificates
+  // are those of the float64 vector kernels)
+  ia.digits = precise && !guard ? 1 : 0;
   ia.mat = mat ? 1 : 0;
   ia.ctrl = L.ctrl;
   HIP_TRY(launch_ingest(ia, maxpad, st));
@@ -377,6 +383,8 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     ca.pad0 = L.pad[0]; ca.pad1 = L.pad[1];
     HIP_TRY(launch_cost(ca, st));
   }
+  int n_dig = 0;   // lanes with digit records
+  for (int t = 0; t < W; ++t) n_dig += lanes[t].dig;
   // uniform lane shapes: work item -> slot is a division, no table lookup
   bool uniform = true;
   for (int t = 1; t < W; ++t)
@@ -445,6 +453,7 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     Launch l;
     std::memset(&l, 0, sizeof(l));
     l.dp = L.dp; l.rbmax = L.rbmax; l.mode = mode; l.rows = L.rows;
+    l.ashift = L.ashift; l.abmax = L.abmax;
     l.tau_screen = op->screen_tol > 0.f ? op->screen_tol : op->tol;
     l.tol = op->tol;
     l.slot = L.bank[bank].slot; l.dec = L.bank[bank].dec;
@@ -484,7 +493,10 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     // items with 2 tiles per group, 128 with 4, 256 with 32)
     if (precise) {
       const int tg = tpg[role];
-      if ((tg >= 16 && items <= 256) || (tg >= 4 && items <= 128) || (tg >= 2 && items <= 64))
+      // (the most items a launch's partials hold; without guarded release a
+      // check pass rides along)
+      const int most = guard ? kSplitItems : kSplitSlots / 2;
+      if ((tg >= 16 && items <= most) || (tg >= 4 && items <= 128) || (tg >= 2 && items <= 64))
         return VAR_SPLIT;
     }
     // (the float64 kernel's items hold 64 to 256 rows: fewer items per width)
@@ -495,9 +507,29 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     if (items < medium) return VAR_NARROW;
     return (use_mfma && tpg[role] <= 2) ? VAR_MEDIUM4 : VAR_MEDIUM;
   };
+  // Digit kernel: every layout computes the same bits, on blocks of four waves
+  // (eight in DIG_1X8). Row tiles on their own blocks start and finish side by
+  // side, so they come first as long as all blocks of the launch -- of all
+  // sub-batches' launches -- fit on the chip at once (256 CUs times the waves per
+  // SIMD); past that, more rows per block share the column loads and the fixed
+  // costs of a block. Measured us per cycle with 1X4 / 2X2 / 4X1: mixture lanes
+  // (d = 8) at 10 lanes 21.4 / 21.6 / 31.5, 24 lanes 26.1 / 29.6 / 31.5, 64 lanes
+  // 51.9 / 42.4 / 37.9; telemetry lanes (d = 16) at 4 lanes 17.2 / 21.6 / 28.7, 64
+  // lanes 38.3 / 27.5 / 42.1, 256 lanes 154 / 106 / 82. Eight shares of the
+  // columns pay for long sweeps of few rows: one LiDAR lane of 4096 points 23.5
+  // against 26.5 with four, one mixture lane of 1024 points 17.5 against 16.9.
+  auto pick_dig = [&](int items, int role) -> int {
+    const int room = 256 * dig_waves_per_simd(d);
+    const int tiles = items * parts;
+    if (tiles <= 64 && tpg[role] >= 8) return DIG_1X8;
+    if (4 * tiles <= room) return DIG_1X4;
+    if (2 * tiles <= room) return DIG_2X2;
+    return DIG_4X1;
+  };
   auto blocks_of = [&](int items) -> int { return std::max(items, 0); };
   int seqno = 0;   // update launches issued (see HostSnap::progress)
-  auto run = [&](Launch l, int variant, int blocks, bool sample, int cycle, int kind) -> ds_err {
+  auto run = [&](Launch l, int variant, int vdig, int blocks, bool sample, int cycle,
+                 int kind) -> ds_err {
     l.seqno = ++seqno;
     const bool timed = tm.on && sample && (int)timed_launches.size() < kMaxTimed;
     // the events are part of the kernel's own dispatch: they time the kernel,
@@ -505,7 +537,14 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     const int e0 = timed ? tm.take() : -1, e1 = timed ? tm.take() : -1;
     hipEvent_t h0 = e0 >= 0 ? (*tm.pool)[e0] : nullptr, h1 = e1 >= 0 ? (*tm.pool)[e1] : nullptr;
     if (mat) HIP_TRY(launch_update_mat(l, blocks, st, h0, h1));
-    else if (precise) HIP_TRY(launch_update_f64(l, d, variant, blocks, st, h0, h1));
+    else if (precise) {
+      // each kernel takes the items of its own lanes; a window almost always
+      // holds one kind only. The events of a timed launch go to the first.
+      if (n_dig > 0) HIP_TRY(launch_update_dig(l, d, vdig, blocks, st, h0, h1));
+      if (n_dig < W)
+        HIP_TRY(launch_update_f64(l, d, variant, blocks, st, n_dig > 0 ? nullptr : h0,
+                                  n_dig > 0 ? nullptr : h1));
+    }
     else if (d > kMaxDSmall) HIP_TRY(launch_update_mfma_k(l, blocks, st, h0, h1));
     else HIP_TRY(launch_update(l, d, use_mfma, variant, blocks, st, h0, h1));
     if (timed) {
@@ -573,9 +612,9 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
       MoveArgs ma;
       std::memset(&ma, 0, sizeof(ma));
       ma.src = L.bank[bank]; ma.dst = L.bank[bank ^ 1]; ma.ctrl = L.ctrl;
-      ma.A = A; ma.dp = L.dp; ma.compact = 1; ma.emit_all = 0; ma.mode = mode;
+      ma.A = A; ma.d = L.d; ma.dp = L.dp; ma.compact = 1; ma.emit_all = 0; ma.mode = mode;
       ma.pad[0] = L.pad[0]; ma.pad[1] = L.pad[1];
-      ma.n_max = pr->n_max; ma.m_max = pr->m_max; ma.chunk = 1024; ma.es = L.es; ma.rbmax = L.rbmax;
+      ma.n_max = pr->n_max; ma.m_max = pr->m_max; ma.chunk = 1024; ma.es = L.es; ma.abmax = L.abmax;
       ma.f = res->f; ma.g = res->g; ma.depth = res->depth; ma.residual = res->residual;
       ma.row_res = res->row_residual; ma.col_res = res->col_residual; ma.status = res->status;
       HIP_TRY(launch_move(ma, A, maxpad, st));
@@ -599,7 +638,7 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     if (audit_prev && guard) lf.p[0].gerr_out = L.gerr[0];
     const int vf = pick(items[0], 0);
     lf.nb0 = blocks_of(items[0]);
-    ds_err r = run(lf, vf, lf.nb0, sample, k, 0);
+    ds_err r = run(lf, vf, pick_dig(items[0], 0), lf.nb0, sample, k, 0);
     if (r != DS_OK) return r;
     if (audit_prev && guard) {
       // guarded release: float64 verification of state k-1 (the potentials the
@@ -625,7 +664,7 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
       lr.p[0].depth = k - 1;
       lr.p[0].verify_all = 1;
       lr.nb0 = blocks_of(items[0]);
-      r = run(lr, pick(items[0], 0), lr.nb0, false, k, 1);
+      r = run(lr, pick(items[0], 0), pick_dig(items[0], 0), lr.nb0, false, k, 1);
       if (r != DS_OK) return r;
     }
     // g-half of cycle k (+ column check and decision for state k-1)
@@ -649,7 +688,7 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     }
     // guarded release: the export rounding of state k's g, for its audit
     if (guard && k % ae == 0) lg.p[0].gerr_out = L.gerr[1];
-    r = run(lg, vg, blocks, sample, k, 0);
+    r = run(lg, vg, pick_dig(items[1], 1), blocks, sample, k, 0);
     if (r != DS_OK) return r;
     launched = k;
   }
@@ -684,14 +723,14 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
       lv.p[0].final_audit = 1; lv.p[0].depth = K; lv.p[0].verify_all = 1;
       const int vv = pick(ctrl.items_f, 0);
       lv.nb0 = blocks_of(ctrl.items_f);
-      ds_err r = run(lv, vv, lv.nb0, true, K, 1);
+      ds_err r = run(lv, vv, pick_dig(ctrl.items_f, 0), lv.nb0, true, K, 1);
       if (r != DS_OK) return r;
       Launch lw = make_launch();
       lw.p[0] = make_pass(1, 1, pK, pK, pK);
       lw.p[0].final_audit = 1; lw.p[0].decide = 1; lw.p[0].depth = K; lw.p[0].verify_all = 1;
       const int vw = pick(ctrl.items_g, 1);
       lw.nb0 = blocks_of(ctrl.items_g);
-      r = run(lw, vw, lw.nb0, true, K, 1);
+      r = run(lw, vw, pick_dig(ctrl.items_g, 1), lw.nb0, true, K, 1);
       if (r != DS_OK) return r;
     }
     A = saveA;
@@ -703,10 +742,10 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     MoveArgs ma;
     std::memset(&ma, 0, sizeof(ma));
     ma.src = L.bank[bank]; ma.dst = L.bank[bank ^ 1]; ma.ctrl = L.ctrl;
-    ma.A = A; ma.dp = L.dp; ma.compact = 0; ma.emit_all = (mode == DS_MODE_STATIC); ma.mode = mode;
+    ma.A = A; ma.d = L.d; ma.dp = L.dp; ma.compact = 0; ma.emit_all = (mode == DS_MODE_STATIC); ma.mode = mode;
     ma.final_par = ctrl.final_cycle & 1;
     ma.pad[0] = L.pad[0]; ma.pad[1] = L.pad[1];
-    ma.n_max = pr->n_max; ma.m_max = pr->m_max; ma.chunk = 1024; ma.es = L.es; ma.rbmax = L.rbmax;
+    ma.n_max = pr->n_max; ma.m_max = pr->m_max; ma.chunk = 1024; ma.es = L.es; ma.abmax = L.abmax;
     ma.f = res->f; ma.g = res->g; ma.depth = res->depth; ma.residual = res->residual;
     ma.row_res = res->row_residual; ma.col_res = res->col_residual; ma.status = res->status;
     HIP_TRY(launch_move(ma, A, maxpad, st));

@@ -45,12 +45,14 @@ constexpr int kGroups = 8;       // fixed column groups of a lane (whole tiles e
 // in order, so that a narrow launch can give every (work item, sub-group) a
 // wave of its own (k_update_f64_split, one block per group) with the same bits.
 constexpr int kSubGroups = 4;
-// most work items of one pass of a split launch; a launch holds at most two
-// passes, and its partials (in the workspace) are sized for both
+// most work items of one pass of a split launch, and of the whole launch (its
+// partials in the workspace hold that many: 224 items with a check pass beside
+// the update, the full 256 without)
 constexpr int kSplitItems = 256;
-constexpr int kSplitSlots = 2 * kSplitItems;
+constexpr int kSplitSlots = 448;
 constexpr int kRowsMfma = 32;    // rows per work item, matrix-core kernel
 constexpr int kRowsValu = 64;    // rows per work item, vector-ALU kernel
+constexpr int kRowsDig = 32;     // rows of a digit tile; the aggregates' unit, float64 state
 constexpr int kRowsMfmaK = 128;  // rows per work item, matrix-free large-d kernel
 constexpr int kMfreeCols = 128;  // columns per step of the matrix-free large-d kernel
 // coordinates per LDS stage of the matrix-free large-d kernel; its point
@@ -71,6 +73,16 @@ constexpr float kFastRange = 64.f;  // max spread of the bound (log2 units) for 
 // far above the true row maximum) is rounded once to float32 for v_exp_f32,
 // a relative error of at most 64 * 2^-24 * ln 2 ~ 2.6e-6 per term.
 constexpr float kFastRangePrecise = 64.f;
+// Float64 state, digit records: a lane whose exponents stay within kDigRange
+// (bounded at ingest from its points, masses and proposal) keeps each scaled
+// coordinate as four float16 digits, and every exponent is formed from them on
+// the float16 matrix cores (see k_update_dig); the other lanes keep doubles.
+// With digits on the grids 2^-3, 2^-15, 2^-27, 2^-39 the products of the
+// leading digits and of the potentials' leading part are multiples of 2^-6, so
+// their float32 sums are exact while they stay below 2^18 (and a column operand or
+// anchor, at most half of the range, below 2^17).
+constexpr double kDigRange = 250000.0;
+constexpr double kDigCoord = 255.75;   // largest coordinate: 11 bits above 2^-3
 constexpr int kMaxTimed = 4096;     // timed launches per sub-batch (DS_F_TIMING)
 constexpr size_t kScratchBytes = (size_t)64 << 20;  // workspace of ds_solve_noalloc, per GPU
 constexpr int kMaxDevices = 64;
@@ -99,7 +111,8 @@ struct SlotInfo {
   int passed;      // static mode: first passing audit seen (lane keeps updating)
   float kappa;     // log2(e) / eps
   double kappa64;  // the same in float64 (precise state)
-  int pad[2];
+  int dig;         // float64 state: digit records (see kDigRange), else plain doubles
+  int pad;
 };
 
 // Control block (device). Counters written by kernels, read by the host.
@@ -175,7 +188,7 @@ struct Bank {
   float* gam[2][2];  // [side][parity] [W][pad]; -inf for dead points
   SlotInfo* slot;    // [W]
   Decision* dec;     // [W]
-  float4* agg[4];    // [W][rbmax] row-block aggregates by slot
+  float4* agg[4];    // [W][abmax] row-block aggregates by slot
   // Work item order of the mixed-shape launches, per role (0: f-half and row
   // check, 1: g-half and column check): the slots by decreasing column count
   // (the length of each of the lane's sweeps), then by slot. Launches place
@@ -191,6 +204,7 @@ struct Layout {
   int pad[2];        // npad, mpad
   int rbmax;         // max row blocks of either side
   int rows;          // rows per work item (kernel dependent)
+  int ashift, abmax; // log2 of the rows per aggregate (at most `rows`), aggregates per lane side
   Bank bank[2];
   float* center;     // [W][d] (ingest only)
   int* vcnt;         // [W] column-check arrival counters
@@ -232,6 +246,11 @@ __host__ __device__ constexpr int rows_f64(int) { return 128; }
 __host__ __device__ inline int row_blocks(int nrows, int rows) { return (nrows + rows - 1) / rows; }
 
 
+// aggregates of one lane-side (a shift: every block takes this on its way in)
+__host__ __device__ inline int agg_blocks(int nrows, int ashift) {
+  return (nrows + (1 << ashift) - 1) >> ashift;
+}
+
 // ------------------------------------------------------ kernel arguments
 // One pass = one half-step (kind 0) or one marginal check (kind 1) over the
 // slots of the current bank. A launch runs one or two passes.
@@ -246,7 +265,7 @@ struct Pass {
   const float* w_row;     // caller masses of the row side, [W][w_ld] by lane id
   const int* off;         // [A + 1] first work item of each position of `ord` (ipl == 0)
   const int* ord;         // [A] slots in item order (see Bank::ord)
-  float4* agg_out;        // [W][rbmax] this pass's row-block aggregates
+  float4* agg_out;        // [W][abmax] this pass's row-block aggregates
   float4* gerr_out;       // update kind, guarded release with the float64 state: the
                           // export rounding of this side's potentials, by caller lane
   const float4* agg_bound;   // update: the column side's latest update aggregates
@@ -267,6 +286,7 @@ struct Launch {
   Pass p[2];
   int nb0;                // blocks of pass 0; the rest belong to pass 1
   int dp, rbmax, mode, rows;
+  int ashift, abmax;      // log2 of the rows per aggregate, aggregates per lane side
   float tau_screen, tol;
   SlotInfo* slot;
   Decision* dec;
@@ -326,10 +346,10 @@ struct ScanArgs {          // compaction map over the slots of the current bank
 struct MoveArgs {
   Bank src, dst;
   const Ctrl* ctrl;       // compaction: iterate the slots of the width before the map
-  int A, dp, compact, emit_all, mode;
+  int A, d, dp, compact, emit_all, mode;
   int pad[2];
   int es;                 // state element size in floats (1 or 2)
-  int rbmax;              // row-block aggregates per slot
+  int abmax;              // aggregates per slot
   int n_max, m_max;
   int final_par;          // parity of the final state (static mode emission)
   int chunk;              // points per block per side
@@ -346,6 +366,7 @@ struct IngestArgs {
   int W, n_max, m_max, d, dp, dh;
   int pad[2];
   int precise;            // float64 state
+  int digits;             // float64 state: digit records for the lanes that allow them
   int mat;                // materialised cost: no records, cold start gam^y = 0
   Bank bank;
   float* center;
@@ -353,7 +374,7 @@ struct IngestArgs {
   int* nchk;
   float* disc;
   RowCert* row64;        // guarded release: cleared (depth 0 matches no audit)
-  int rbmax;
+  int abmax;
   Ctrl* ctrl;
 };
 
@@ -365,10 +386,19 @@ enum { VAR_NARROW = 0,   // 32-row items, one group per wave (8 waves)
                          // kernel, lanes of at most 2 column tiles per group
        VAR_SPLIT = 4 };  // float64 kernel: a block per (item, group), a wave per sub-group, at most
                          // kSplitItems items per pass
+// Digit kernel: row tiles x column shares of a block (a wave each).
+enum { DIG_1X8 = 0, DIG_1X4 = 1, DIG_2X2 = 2, DIG_4X1 = 3 };
+// its waves per SIMD (the register budget): three hide more of the matrix
+// instructions behind the vector work than two (probe loops: 377 against 414
+// cycles per 1024 terms), while the row operands of d > 8 take two waves' registers
+constexpr int dig_waves_per_simd(int d) { return d <= 8 ? 3 : 2; }
 // e0 / e1 (may be null): events that record the kernel's own start and end
 hipError_t launch_update(const Launch& a, int d, bool use_mfma, int variant, int blocks,
                          hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_update_f64(const Launch& a, int d, int variant, int blocks, hipStream_t st,
+                             hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// the same half-step for the lanes with digit records
+hipError_t launch_update_dig(const Launch& a, int d, int variant, int blocks, hipStream_t st,
                              hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // matrix-free matrix-core half-step for any d (tiled contraction), `blocks`
 // work items over both passes

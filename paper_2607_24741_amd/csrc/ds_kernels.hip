@@ -1,7 +1,16 @@
 // gfx950 kernels of the active-set batched Sinkhorn path (wave64, CDNA4).
 //
-//  k_update_f64<D, GW>
+//  k_update_dig<D, RG, GS>
 //                     one half-step of eq:sinkhorn-cycle for every (slot, row
+//                     block) work item with the state in float64, every exponent
+//                     formed from float16 digits of its factors on the matrix
+//                     cores (exact where it matters) and rounded once to float32
+//                     for v_exp_f32 (the default path for d <= 16, for every lane
+//                     whose exponents fit the digits' range).
+//  k_update_f64<D, GW>
+//                     the same half-step with the exponents on the vector ALU,
+//                     for guarded release and the lanes out of that range: one
+//                     half-step of eq:sinkhorn-cycle for every (slot, row
 //                     block) work item with the state in float64: every
 //                     exponent formed in float64 on the vector ALU (d fused
 //                     multiply-adds and an add) and rounded once to float32
@@ -9,8 +18,7 @@
 //                     two rows per lane up to d = 12, streaming base-2
 //                     log-sum-exp over 8 fixed column groups of 4 fixed
 //                     sub-groups each, fused row screen; with a second pass in
-//                     the same launch, the column check and release decision
-//                     (the default path for d <= 16).
+//                     the same launch, the column check and release decision.
 //  k_update_f64_split<D>
 //                     the same half-step for narrow launches: one block per
 //                     (work item, column group), one wave per sub-group, the
@@ -235,11 +243,11 @@ struct LaneAgg {
   float sum, dmin, dmax;
   int bad;
 };
-__device__ __forceinline__ LaneAgg lane_aggregate(const float4* agg, int s, int rbmax, int nrb,
+__device__ __forceinline__ LaneAgg lane_aggregate(const float4* agg, int s, int abmax, int nrb,
                                                   bool coherent) {
   LaneAgg g;
   float t0 = 0.f, t1 = INFINITY, t2 = -INFINITY, t3 = 0.f;
-  const float4* base = agg + (size_t)s * rbmax;
+  const float4* base = agg + (size_t)s * abmax;
   for (int q = (int)(threadIdx.x & 63); q < nrb; q += 64) {
     const float4 v = coherent ? ld_dev4(base + q) : base[q];
     t0 += v.x;
@@ -267,8 +275,8 @@ __device__ __forceinline__ LaneAgg lane_aggregate(const float4* agg, int s, int 
 __device__ __forceinline__ void update_facts(const Launch& L, const Pass& P, int s, int ncols,
                                              bool& fast, float& M, float range = kFastRange) {
   float t1 = INFINITY, t2 = -INFINITY;
-  const float4* base = P.agg_bound + (size_t)s * L.rbmax;
-  const int nrb = row_blocks(ncols, L.rows);
+  const float4* base = P.agg_bound + (size_t)s * L.abmax;
+  const int nrb = agg_blocks(ncols, L.ashift);
   for (int q = (int)(threadIdx.x & 63); q < nrb; q += 64) {
     const float4 v = base[q];
     t1 = fminf(t1, v.y);
@@ -285,11 +293,48 @@ __device__ __forceinline__ bool check_facts(const Launch& L, const Pass& P, int 
                                             float& rhat) {
   rhat = NAN;
   if (P.role == 1 && !P.final_audit) {
-    const LaneAgg g = lane_aggregate(P.agg_screen, s, L.rbmax, row_blocks(n_x, L.rows), false);
+    const LaneAgg g = lane_aggregate(P.agg_screen, s, L.abmax, agg_blocks(n_x, L.ashift), false);
     rhat = g.sum;
     return P.verify_all || !isfinite(g.sum) || g.sum <= L.tau_screen;
   }
   return true;
+}
+
+
+// --------------------------------------------------------- digit records
+// Float64 state, lanes within kDigRange: a scaled coordinate is the exact sum of
+// four float16 digits, h (multiples of 2^-3), l1 (2^-15), l2 (2^-27) and l3
+// (2^-39), each an integer of at most 11 bits and a sign; l2 is stored times
+// 2^12 and l3 times 2^24, so that every stored digit is a float16. A record
+// holds the digits piece by piece: h of every coordinate, then l1, l2, l3 (the
+// size of the doubles they replace). The scaled coordinate is defined as this
+// sum (within 2^-40 of the double).
+// The column operand gam is held the same way, in the 8 bytes of its double:
+// gam = 2^6 k1 + 2^-6 k2 + 2^-18 k3 + 2^-30 k4; a dead point holds k1 = -60000
+// (a term of 2^-3.8e6: zero).
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f16x4 dig_gam(double g) {
+  f16x4 k = {(_Float16)-60000.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+  if (g == -(double)INFINITY) return k;
+  const double k1 = rint(g * 0x1p-6);
+  g = fma(-k1, 0x1p6, g);
+  const double k2 = rint(g * 0x1p6);
+  g = fma(-k2, 0x1p-6, g);
+  const double k3 = rint(g * 0x1p18);
+  g = fma(-k3, 0x1p-18, g);
+  const double k4 = rint(g * 0x1p30);
+  k.x = (_Float16)(float)k1;
+  k.y = (_Float16)(float)k2;
+  k.z = (_Float16)(float)k3;
+  k.w = (_Float16)(float)k4;
+  return k;
+}
+// coordinate k of a digit record of d coordinates (exact in float64)
+__device__ __forceinline__ double dig_coord(const _Float16* r, int d, int k) {
+  return ((double)(float)r[k] + (double)(float)r[d + k]) +
+         ((double)(float)r[2 * d + k] * 0x1p-12 + (double)(float)r[3 * d + k] * 0x1p-24);
 }
 
 // ----------------------------------------------------------- item epilogue
@@ -305,7 +350,8 @@ __device__ __forceinline__ double log2_t(double x) { return log2(x); }
 __device__ __forceinline__ float exp2_t(float x) { return ex2(x); }
 __device__ __forceinline__ double exp2_t(double x) { return exp2(x); }
 
-template <int UNIT, int NU, int R, typename T>
+// DIG: digit lanes (T = double): the new column operand is stored as digits.
+template <int UNIT, int NU, int R, typename T, bool DIG = false>
 __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotInfo& si, int rb0,
                               const bool (&owner)[R], const bool (&live)[R], bool fast, float Mf,
                               const T (&lse_old)[R], const T (&lm)[R], const float (&w)[R],
@@ -316,6 +362,9 @@ __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotI
   const int lane = threadIdx.x & 63;
   const int nrows = P.role ? si.m : si.n;
   const int nrb = row_blocks(nrows, UNIT);
+  // aggregates per UNIT rows: beside digit lanes the float64 vector kernels'
+  // 128-row blocks take the first of their four units and leave the others empty
+  const int apu = sizeof(T) == 8 && UNIT > kRowsDig ? UNIT >> L.ashift : 1;
   const bool frozen = (L.mode == MODE_LOGICAL) && si.done;
   const T M = (T)Mf;
   float rho = 0.f, dmin = INFINITY, dmax = -INFINITY, bad = 0.f;
@@ -364,11 +413,14 @@ __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotI
     }
   }
   const int nu = min(NU, nrb - rb0);
-  float4* dst = P.agg_out + (size_t)s * L.rbmax + rb0;
+  float4* dst = P.agg_out + (size_t)s * L.abmax + rb0 * apu;
   const bool deciding = P.kind == KIND_VERIFY && P.role == 1 && P.decide;
   if (!deciding) {
-    if (lane == 0)
+    if (apu > 1) {
+      if (lane < apu) dst[lane] = lane ? make_float4(0.f, INFINITY, -INFINITY, 0.f) : ag[0];
+    } else if (lane == 0) {
       for (int u = 0; u < nu; ++u) dst[u] = ag[u];
+    }
     // the new state goes out last: nothing after it reuses its registers, so
     // the wave ends without waiting for the stores
     if (P.kind == KIND_UPDATE && !frozen) {
@@ -377,7 +429,8 @@ __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotI
         if (!owner[r]) continue;
         const size_t idx = (size_t)s * P.padr + rb0 * UNIT + 64 * r + lane;
         reinterpret_cast<T*>(P.lse_out)[idx] = lse_new[r];
-        reinterpret_cast<T*>(P.gam_out)[idx] = gam_new[r];
+        if (DIG) reinterpret_cast<f16x4*>(P.gam_out)[idx] = dig_gam((double)gam_new[r]);
+        else reinterpret_cast<T*>(P.gam_out)[idx] = gam_new[r];
       }
     }
     return;
@@ -386,6 +439,7 @@ __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotI
   int last = 0;
   if (lane == 0) {
     for (int u = 0; u < nu; ++u) st_dev4(dst + u, ag[u]);
+    for (int u = 1; u < apu; ++u) st_dev4(dst + u, make_float4(0.f, INFINITY, -INFINITY, 0.f));
     wait_mem();
     const int prev = atomicAdd(&L.vcnt[si.lane], nu);
     last = (prev + nu == nrb);
@@ -394,16 +448,16 @@ __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotI
   last = __builtin_amdgcn_readfirstlane(last);
   if (!last) return;
   // last item of a checked lane: column residual and the decision
-  const LaneAgg gc = lane_aggregate(P.agg_out, s, L.rbmax, nrb, true);
+  const LaneAgg gc = lane_aggregate(P.agg_out, s, L.abmax, agg_blocks(nrows, L.ashift), true);
   float rrow = rhat;
   if (P.final_audit) {
-    const LaneAgg gr = lane_aggregate(P.agg_rowchk, s, L.rbmax, row_blocks(si.n, UNIT), false);
+    const LaneAgg gr = lane_aggregate(P.agg_rowchk, s, L.abmax, agg_blocks(si.n, L.ashift), false);
     rrow = gr.sum;
   } else if (L.disc) {
     // shadow mode: the row marginal of the audited state was also recomputed
     // by a dedicated check pass; record how far the screen is from it where a
     // release can be decided (either value within twice the tolerance)
-    const LaneAgg gr = lane_aggregate(P.agg_rowchk, s, L.rbmax, row_blocks(si.n, UNIT), false);
+    const LaneAgg gr = lane_aggregate(P.agg_rowchk, s, L.abmax, agg_blocks(si.n, L.ashift), false);
     const float dsc = fabsf(rhat - gr.sum);
     if (lane == 0 && dsc == dsc && fminf(rhat, gr.sum) <= 2.f * L.tol)
       // non-negative floats order as their bit patterns
@@ -1538,6 +1592,7 @@ void k_update_f64(Launch L) {
     update_facts(L, P, s, ncols, fast, M, kFastRangePrecise);
     if (!item_live(L, P, s, si, c_fin, c_A)) return;
   }
+  if (si.dig) return;   // k_update_dig's
   bool live[R];
   double bias[R];
 #pragma unroll
@@ -1723,6 +1778,7 @@ void k_update_f64_split(Launch L) {
     update_facts(L, P, s, ncols, fast, M, kFastRangePrecise);
     work = item_live(L, P, s, si, c_fin, c_A);
   }
+  if (si.dig) return;   // k_update_dig_split's: none of the item's blocks arrives
   bool live[R];
   double bias[R];
 #pragma unroll
@@ -1819,6 +1875,496 @@ void k_update_f64_split(Launch L) {
   finish_rows_r<ROWS, 1, R, double>(L, P, s, si, rb, owner, lo, fast, M, lse_old, lm, w, Mt, St,
                                     rhat, gkeep);
   if (P.gerr_out) f64_export_rounding<D, R>(L, P, si, rb, owner, w, lm, lse_old, gkeep, xr);
+}
+
+// ------------------------------------------------ float64 half-step from digits
+// The float64-state half-step of the lanes with digit records: the exponent
+// z_ij = gam_j + x~_i . y~_j - anchor_i of every term is formed on the float16
+// matrix cores from the digits of its factors. With x~ = h + l1 + l2 + l3 (and
+// y~ likewise) and gam and -anchor as digits k1..k4, the products go by size:
+//   A  h.h and the k1, k2       multiples of 2^-6: exact in float32
+//   B  h.l1 + l1.h              multiples of 2^-18
+//   C  h.l2 + l1.l1 + l2.h and the k3, k4     at most about 2^-6
+//   D  h.l3 + l1.l2 + l2.l1 + l3.h            at most about 2^-19
+// (what is left out is below 2^-31). A then B share one accumulator: its sum is
+// exact while |z| < 64, that is for every term above 2^-64 of its anchor. C and D
+// share a second one, scaled by 2^12 so that every digit is a float16, and
+// z = AB + 2^-12 CD is rounded once, as the float64 vector path rounds its
+// exponent: the two agree up to a rounding that falls the other way now and then
+// (z is within about 2^-30 of the exact exponent before it is rounded).
+//
+// A point fills NS = 4 D + 8 of the contraction's K slots, in chunks of 16 (one
+// v_mfma_f32_32x32x16_f16 each): its digits [h l1 l2 l3], its operand's k1..k4,
+// and four powers of two that weigh the row anchor's digits. The column side is
+// loaded in that order, once per tile; the row side holds one operand per level
+// and chunk whose slots carry the partner digit (a power of two for k, a digit
+// of the anchor) and zeros.
+//
+// In a 32 x 32 tile lane l holds row l % 32 and 16 of the columns; the tile's
+// columns are dealt so that the lanes below 32 hold the even ones and the lanes
+// from 32 on the odd ones, in order. Sums then run in the order of the float64
+// vector kernels: even and odd columns of a tile in float32, the tile's two sums
+// added in float32 (a lane swap) and added in float64 to the sub-group's sum;
+// sub-groups fold into groups, groups in order. The bits depend on the lane alone.
+template <int D>
+struct Dig {
+  static constexpr int DP = D + (D & 1);
+  // where the four digits fill their chunks with the operand (d = 3, 7, ..) the row
+  // anchor enters as the accumulators' start values instead of as K slots: one
+  // matrix instruction less in A and C each (d = 3: 4 instead of 6)
+  static constexpr bool SPLAT = D % 4 == 3;
+  static constexpr int NS = SPLAT ? 4 * D + 4 : 4 * D + 8;   // K slots of a point
+  static constexpr int NC = (NS + 15) / 16;     // chunks of 16
+  static constexpr int REC = 4 * DP;            // float16 per record
+  // source of the row operand in (level, slot): -1 zero; below 900 a form of a
+  // coordinate (form * 64 + coordinate); 1000 + e the power 2^e; 2000 + b digit b
+  // of the anchor
+  enum { H = 0, L1 = 1, L2 = 2, L1S = 3, L3D = 4, HD = 5 };
+  static constexpr int src(int level, int slot) {
+    if (slot >= 4 * D + 4) {
+      const int b = slot - 4 * D - 4;
+      if (level == 0) return b < 2 ? 2000 + b : -1;
+      if (level == 2) return b == 2 || b == 3 ? 2000 + b : -1;
+      return -1;
+    }
+    if (slot >= 4 * D) {
+      const int k = slot - 4 * D;
+      if (level == 0) return k == 0 ? 1000 + 6 : k == 1 ? 1000 - 6 : -1;
+      if (level == 2) return k == 2 ? 1000 - 6 : k == 3 ? 1000 - 18 : -1;   // times 2^12
+      return -1;
+    }
+    const int q = slot / D, k = slot % D;
+    if (q > level) return -1;
+    const int form[4][4] = {{H, 0, 0, 0}, {L1, H, 0, 0}, {L2, L1S, H, 0}, {L3D, L2, L1, HD}};
+    return form[level][q] * 64 + k;
+  }
+  // whether the row operand of (level, chunk) has any slot
+  static constexpr bool used(int level, int chunk) {
+    for (int s = 16 * chunk; s < 16 * chunk + 16; ++s)
+      if (src(level, s) >= 0) return true;
+    return false;
+  }
+  // where the anchor's digits sit: slots 4 (D + 1) .. + 3
+  static constexpr int AC = (D + 1) / 4, AH = ((D + 1) / 2) & 1, AP = (D + 1) & 1;
+};
+constexpr float dig_pow2(int e) {
+  float v = 1.f;
+  for (; e > 0; --e) v *= 2.f;
+  for (; e < 0; ++e) v *= 0.5f;
+  return v;
+}
+
+// column tiles loaded ahead: a launch starts with cold caches, and a tile comes
+// from beyond the L2 in about the time of two
+template <int D>
+constexpr int dig_prefetch() { return D <= 4 ? 4 : D <= 8 ? 3 : 2; }
+// The row operands of one 32-row tile, this lane's row and half.
+template <int D>
+struct DigRow {
+  static constexpr int NC = Dig<D>::NC;
+  f16x8 x[4][NC];
+  template <int LEVEL, int SLOT>
+  static __device__ __forceinline__ _Float16 slot(const _Float16 (&f)[6][D]) {
+    constexpr int s = Dig<D>::src(LEVEL, SLOT);
+    if constexpr (s < 0 || s >= 2000) return (_Float16)0.f;
+    else if constexpr (s >= 900) return (_Float16)dig_pow2(s - 1000);
+    else return f[s / 64][s % 64];
+  }
+  // four slots of one half at once (d a multiple of 4: they share a digit)
+  template <int LEVEL, int S4>
+  static __device__ __forceinline__ f16x4 slot4(const f16x4 (&f)[6][(D + 3) / 4]) {
+    constexpr int s = Dig<D>::src(LEVEL, 4 * S4);
+    if constexpr (S4 < D) {
+      if constexpr (s < 0) return f16x4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+      else return f[s / 64][(s % 64) / 4];
+    } else {
+      return f16x4{slot_const<LEVEL, 4 * S4>(), slot_const<LEVEL, 4 * S4 + 1>(),
+                   slot_const<LEVEL, 4 * S4 + 2>(), slot_const<LEVEL, 4 * S4 + 3>()};
+    }
+  }
+  template <int LEVEL, int SLOT>
+  static __device__ __forceinline__ _Float16 slot_const() {
+    constexpr int s = Dig<D>::src(LEVEL, SLOT);
+    return (s >= 900 && s < 2000) ? (_Float16)dig_pow2(s >= 900 && s < 2000 ? s - 1000 : 0)
+                                  : (_Float16)0.f;
+  }
+  template <int LEVEL, int C, int E>
+  __device__ __forceinline__ void fill(const _Float16 (&f)[6][D], int h) {
+    const _Float16 lo = slot<LEVEL, 16 * C + E>(f), hi = slot<LEVEL, 16 * C + 8 + E>(f);
+    x[LEVEL][C][E] = h ? hi : lo;
+    if constexpr (E + 1 < 8) fill<LEVEL, C, E + 1>(f, h);
+    else if constexpr (C + 1 < NC) fill<LEVEL, C + 1, 0>(f, h);
+    else if constexpr (LEVEL + 1 < 4) fill<LEVEL + 1, 0, 0>(f, h);
+  }
+  template <int LEVEL, int C>
+  __device__ __forceinline__ void fill4(const f16x4 (&f)[6][(D + 3) / 4], int h) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    auto pick = [&](f16x4 lo, f16x4 hi) {
+      const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
+      return __builtin_bit_cast(f16x4, u32x2{h ? b.x : a.x, h ? b.y : a.y});
+    };
+    const f16x4 p0 = pick(slot4<LEVEL, 4 * C>(f), slot4<LEVEL, 4 * C + 2>(f));
+    const f16x4 p1 = pick(slot4<LEVEL, 4 * C + 1>(f), slot4<LEVEL, 4 * C + 3>(f));
+    x[LEVEL][C] = __builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, 6, 7);
+    if constexpr (C + 1 < NC) fill4<LEVEL, C + 1>(f, h);
+    else if constexpr (LEVEL + 1 < 4) fill4<LEVEL + 1, 0>(f, h);
+  }
+  __device__ __forceinline__ void load(const _Float16* rec, int h) {
+    const _Float16 up = (_Float16)4096.f, down = (_Float16)0x1p-12f;
+    if constexpr (D % 4 == 0) {
+      f16x4 f[6][D / 4];
+#pragma unroll
+      for (int k = 0; k < D / 4; ++k) {
+        const f16x4* v = reinterpret_cast<const f16x4*>(rec) + k;
+        const f16x4 a = v[0], b = v[D / 4], c = v[2 * (D / 4)], e = v[3 * (D / 4)];
+        f[Dig<D>::H][k] = a;
+        f[Dig<D>::L1][k] = b;
+        f[Dig<D>::L2][k] = c;
+        f[Dig<D>::L1S][k] = b * up;
+        f[Dig<D>::L3D][k] = e * down;
+        f[Dig<D>::HD][k] = a * down;
+      }
+      fill4<0, 0>(f, h);
+    } else {
+      constexpr int NV = Dig<D>::REC / 8;
+      f16x8 v[NV];
+#pragma unroll
+      for (int q = 0; q < NV; ++q) v[q] = reinterpret_cast<const f16x8*>(rec)[q];
+      _Float16 f[6][D];
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        const _Float16 a = v[k / 8][k % 8], b = v[(D + k) / 8][(D + k) % 8];
+        const _Float16 c = v[(2 * D + k) / 8][(2 * D + k) % 8];
+        const _Float16 e = v[(3 * D + k) / 8][(3 * D + k) % 8];
+        f[Dig<D>::H][k] = a;
+        f[Dig<D>::L1][k] = b;
+        f[Dig<D>::L2][k] = c;
+        f[Dig<D>::L1S][k] = b * up;
+        f[Dig<D>::L3D][k] = e * down;
+        f[Dig<D>::HD][k] = a * down;
+      }
+      fill<0, 0, 0>(f, h);
+    }
+  }
+  float hi, lo;   // SPLAT: minus the anchor, its multiple of 2^-6 and the rest times 2^12
+  // the row's anchor (finite)
+  __device__ __forceinline__ void anchor(double a, int h) {
+    if constexpr (Dig<D>::SPLAT) {
+      const double g = rint(-a * 0x1p6) * 0x1p-6;
+      hi = (float)g;
+      lo = (float)((-a - g) * 0x1p12);
+      return;
+    }
+    const f16x4 k = dig_gam(-a);
+    const _Float16 z = (_Float16)0.f;
+    // (the other half's slots there are its own: they stay)
+    if constexpr (!Dig<D>::SPLAT) {
+      const bool mine = h == Dig<D>::AH;
+      constexpr int e = 4 * Dig<D>::AP;
+      f16x8& xa = x[0][Dig<D>::AC];
+      f16x8& xc = x[2][Dig<D>::AC];
+      xa[e] = mine ? k.x : xa[e];
+      xa[e + 1] = mine ? k.y : xa[e + 1];
+      xc[e + 2] = mine ? k.z : xc[e + 2];
+      xc[e + 3] = mine ? k.w : xc[e + 3];
+    }
+  }
+};
+
+// The column operand of a tile, this lane's column and half. Each chunk is two
+// 8-byte parts; part p of half h holds the slots 4 s4 .. 4 s4 + 3, s4 = 4 c + 2 h
+// + p: digits below s4 = D, the operand's k at it, then the anchor's weights,
+// then nothing (any finite value).
+template <int D>
+struct DigCols {
+  static constexpr int NC = Dig<D>::NC;
+  static constexpr int RB = 2 * Dig<D>::REC;   // bytes per record
+  const char* rec;    // the lane's column records, this column of tile 0, this half
+  const char* gam;    // and its operands
+  bool hi;
+  __device__ __forceinline__ DigCols(const void* rec_lane, const void* gam_lane, int lane) {
+    const int r = lane & 31;
+    const int c = 2 * (4 * (r >> 3) + (r & 3)) + ((r >> 2) & 1);   // tile row r's column
+    hi = lane >= 32;
+    rec = reinterpret_cast<const char*>(rec_lane) + (size_t)c * RB + (hi ? 16 : 0);
+    gam = reinterpret_cast<const char*>(gam_lane) + (size_t)c * 8;
+  }
+  static __device__ __forceinline__ f16x4 weights() {
+    return f16x4{(_Float16)64.f, (_Float16)0x1p-6f, (_Float16)0x1p-6f, (_Float16)0x1p-18f};
+  }
+  template <int C, int P>
+  __device__ __forceinline__ f16x4 part(int t) const {
+    constexpr int a = 4 * C + P, b = a + 2;   // s4 of the two halves
+    constexpr bool ca = a < D, cb = b < D;    // digits
+    constexpr bool wb = b == D + 1;           // weights
+    const char* r8 = rec + (size_t)t * (kColTile * RB) + 32 * C + 8 * P;
+    const char* g8 = gam + (size_t)t * (kColTile * 8);
+    if constexpr (ca && cb) return *reinterpret_cast<const f16x4*>(r8);
+    else if constexpr (a > D) return weights();   // (b > D too)
+    else {
+      // one half holds digits or k; the other k, weights or nothing
+      const f16x4 v = *reinterpret_cast<const f16x4*>(ca ? (hi && b == D ? g8 : hi ? r8 - 16 : r8) : g8);
+      if constexpr (wb) {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 u = __builtin_bit_cast(u32x2, v), k = __builtin_bit_cast(u32x2, weights());
+        return __builtin_bit_cast(f16x4, u32x2{hi ? k.x : u.x, hi ? k.y : u.y});
+      } else {
+        return v;
+      }
+    }
+  }
+  template <int C>
+  __device__ __forceinline__ void chunk(int t, f16x8 (&y)[NC]) const {
+    if constexpr (4 * C + 3 < D) {   // digits throughout
+      y[C] = *reinterpret_cast<const f16x8*>(rec + (size_t)t * (kColTile * RB) + 32 * C);
+    } else {
+      const f16x4 p0 = part<C, 0>(t), p1 = part<C, 1>(t);
+      y[C] = __builtin_shufflevector(p0, p1, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+    if constexpr (C + 1 < NC) chunk<C + 1>(t, y);
+  }
+  __device__ __forceinline__ void load(int t, f16x8 (&y)[NC]) const { chunk<0>(t, y); }
+};
+
+// A level's products of one tile on top of acc
+template <int D, int LEVEL>
+__device__ __forceinline__ f32x16 dig_level(const f16x8 (&y)[Dig<D>::NC], const DigRow<D>& x,
+                                            f32x16 acc) {
+#pragma unroll
+  for (int c = 0; c < Dig<D>::NC; ++c)
+    if (Dig<D>::used(LEVEL, c))
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(y[c], x.x[LEVEL][c], acc, 0, 0, 0);
+  return acc;
+}
+__device__ __forceinline__ f32x16 splat16(float v) {
+  return f32x16{v, v, v, v, v, v, v, v, v, v, v, v, v, v, v, v};
+}
+// own value and the other half's (lane ^ 32), the lower half's first
+struct Halves { float lo, hi; };
+__device__ __forceinline__ Halves halves(float v) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+// The tile's anchored sum of a row over its 32 columns, in both halves' lanes.
+template <int D>
+__device__ __forceinline__ float dig_tile(const f16x8 (&y)[Dig<D>::NC], const DigRow<D>& x) {
+  f32x16 ab = dig_level<D, 0>(y, x, splat16(Dig<D>::SPLAT ? x.hi : 0.f));
+  f32x16 cd = dig_level<D, 2>(y, x, splat16(Dig<D>::SPLAT ? x.lo : 0.f));
+  ab = dig_level<D, 1>(y, x, ab);
+  cd = dig_level<D, 3>(y, x, cd);
+  float e = ex2(fmaf(cd[0], 0x1p-12f, ab[0]));
+#pragma unroll
+  for (int v = 1; v < 16; ++v) e += ex2(fmaf(cd[v], 0x1p-12f, ab[v]));
+  const Halves p = halves(e);
+  return p.lo + p.hi;
+}
+// The tile's largest exponent of a row to the precision of A and B
+template <int D>
+__device__ __forceinline__ float dig_tile_max(const f16x8 (&y)[Dig<D>::NC], const DigRow<D>& x) {
+  const f32x16 ab = dig_level<D, 1>(
+      y, x, dig_level<D, 0>(y, x, splat16(Dig<D>::SPLAT ? x.hi : 0.f)));
+  float m = ab[0];
+#pragma unroll
+  for (int v = 1; v < 16; ++v) m = fmaxf(m, ab[v]);
+  return m;
+}
+
+// The partial (maximum, sum) of this lane's row over tiles [t0, t1) without an
+// anchor from the previous cycle: a first sweep finds the row's largest exponent
+// above `base` (the range's own anchor), a second one sums. Leaves the row
+// anchored at `base`.
+template <int D>
+__device__ __forceinline__ void dig_free_range(const DigCols<D>& cols, DigRow<D>& x, double base,
+                                               int t0, int t1, int h, double& m, double& s) {
+  f16x8 y[Dig<D>::NC];
+  float mx = -INFINITY;
+#pragma unroll 1
+  for (int t = t0; t < t1; ++t) {
+    cols.load(t, y);
+    mx = fmaxf(mx, dig_tile_max<D>(y, x));
+  }
+  const Halves p = halves(mx);
+  mx = fmaxf(p.lo, p.hi);
+  // (an exponent below -1e6 is a dead column's)
+  const bool any = mx > -1e6f;
+  m = any ? (double)mx : -(double)INFINITY;
+  s = 0.0;
+  x.anchor(any ? base + m : base, h);
+#pragma unroll 1
+  for (int t = t0; t < t1; ++t) {
+    cols.load(t, y);
+    s += (double)dig_tile<D>(y, x);
+  }
+  if (!any) s = 0.0;
+  x.anchor(base, h);
+}
+
+// Where block b of a pass of nb items works (SUB blocks per item of 128 rows): as
+// place_item, with the part `sub` of the item's rows. Uniform shapes: the blocks
+// of an XCD take one contiguous range of parts.
+template <int SUB>
+__device__ __forceinline__ bool place_dig(const Launch& L, const Pass& P, int nb, int b, int& s,
+                                          int& rb, int& sub, int& nrows, int& ncols, SlotInfo& si,
+                                          int& c_fin, int& c_A) {
+  if (P.ipl > 0) {
+    const int f = xcd_item(b, nb * SUB);
+    const int item = f / SUB;
+    sub = f - item * SUB;
+    s = item / P.ipl;
+    rb = item - s * P.ipl;
+    if (s >= P.A) return false;
+    const int z = (int)__builtin_amdgcn_mbcnt_lo(0u, 0u);   // (see place_item)
+    c_fin = L.ctrl[z].finished;
+    c_A = L.ctrl[z].A;
+    si = L.slot[s + z];
+    nrows = P.nr;
+    ncols = P.nc;
+    return true;
+  }
+  const int item = b / SUB;
+  sub = b - item * SUB;
+  return place_item<1, 0>(L, P, nb, item, s, rb, nrows, ncols, si, c_fin, c_A);
+}
+
+// RG * GS waves per block: RG row tiles of 32 rows (of the item's four; the
+// other tiles are other blocks') times GS shares of the lane's column groups.
+// Wave (rg, 0) finishes row tile rg.
+template <int D, int RG, int GS>
+__global__ __launch_bounds__(64 * RG * GS, (dig_waves_per_simd(D)))
+void k_update_dig(Launch L) {
+  note_progress(L);
+  constexpr int SUB = rows_f64(D) / (kRowsDig * RG);   // blocks per item
+  constexpr int GW = kGroups / GS;
+  constexpr int NC = Dig<D>::NC;
+  constexpr int PF = dig_prefetch<D>();
+  __shared__ double2 sh_part[kGroups][kRowsDig * RG];
+  const int b = blockIdx.x;
+  const int n0 = L.nb0 * SUB;
+  const int pi = b >= n0;
+  const Pass P = L.p[pi];
+  int s, rb, sub, nrows, ncols, c_fin, c_A;
+  SlotInfo si;
+  if (!place_dig<SUB>(L, P, pi ? (int)gridDim.x / SUB - L.nb0 : L.nb0, pi ? b - n0 : b, s, rb, sub,
+                      nrows, ncols, si, c_fin, c_A))
+    return;
+  const int rt0 = rb * (rows_f64(D) / kRowsDig) + sub * RG;   // the block's first row tile
+  if (rt0 * kRowsDig >= nrows) return;
+  const bool upd = P.kind == KIND_UPDATE;
+  float rhat = NAN;
+  if (!upd) {
+    const bool chk = check_facts(L, P, s, P.role ? ncols : nrows, rhat);
+    if (!item_live(L, P, s, si, c_fin, c_A) || !chk) return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5;
+  const int rg = wave % RG, gs = wave / RG;
+  const int row0 = (rt0 + rg) * kRowsDig;
+  // every load of the item goes out before the block waits on any of them
+  const int i = row0 + (lane & 31);
+  const size_t ridx = (size_t)s * P.padr + i;
+  const double lse_old = reinterpret_cast<const double*>(P.lse_in)[ridx];
+  const bool owner = gs == 0 && lane < kRowsDig && i < nrows;
+  double lm = 0.0;
+  float w = 0.f;
+  if (owner) lm = reinterpret_cast<const double*>(P.lm_row)[ridx];
+  const F64Tiling T(ncols);
+  const int ta = min(T.ct, gs * GW * T.tpg), tb = min(T.ct, (gs * GW + GW) * T.tpg);
+  const DigCols<D> cols(reinterpret_cast<const double*>(P.rec_col) + (size_t)s * P.padc * Dig<D>::DP,
+                        reinterpret_cast<const double*>(P.gam_col) + (size_t)s * P.padc, lane);
+  f16x8 y[PF][NC];
+#pragma unroll
+  for (int u = 0; u < PF; ++u) cols.load(min(ta + u, T.ct - 1), y[u]);
+  DigRow<D> x;
+  x.load(reinterpret_cast<const _Float16*>(P.rec_row) + ridx * Dig<D>::REC, h);
+  bool fast = false;
+  float M = 0.f;
+  if (upd) {
+    update_facts(L, P, s, ncols, fast, M, kFastRangePrecise);
+    if (!item_live(L, P, s, si, c_fin, c_A)) return;
+  }
+  if (!si.dig) return;   // k_update_f64's
+  if (owner) w = P.w_row[(size_t)si.lane * P.w_ld + i];
+  // the row's anchor: the old lse for a check, that plus M for an anchored update,
+  // none (0) for a free update and a dead row
+  const bool live = i < nrows && lse_old != (double)INFINITY;
+  const double base = !live ? 0.0 : !upd ? lse_old : fast ? lse_old + (double)M : 0.0;
+  x.anchor(base, h);
+  const double m0 = fast ? 0.0 : -(double)INFINITY;
+  // the row's partials go out by the lower half (both hold the sums)
+  double2* const part = &sh_part[0][rg * kRowsDig + (lane & 31)];
+  constexpr int PS = kRowsDig * RG;   // stride of a group
+  if (row0 >= nrows) {
+    // no row of this wave exists
+  } else if (fast) {
+    // the wave's groups are consecutive tile ranges, swept in one run; at a
+    // sub-group's end its sums fold into the group's, at a group's end those
+    // go to LDS
+    double gsum = 0.0, srun = 0.0;
+    int g = gs * GW;
+    int gend = min(T.ct, ta + T.tpg), send = min(gend, ta + T.tps);
+    auto tile = [&](const f16x8 (&yt)[NC], int t) {
+      srun += (double)dig_tile<D>(yt, x);
+      if (t + 1 == send) {
+        gsum += srun;
+        srun = 0.0;
+        if (send == gend) {
+          if (h == 0) part[g * PS] = make_double2(0.0, gsum);
+          gsum = 0.0;
+          ++g;
+          gend = min(T.ct, gend + T.tpg);
+        }
+        send = min(gend, send + T.tps);
+      }
+    };
+    int t = ta;
+#pragma unroll 1
+    for (; t + PF <= tb; t += PF) {
+      // (past the wave's last tile the last one loads again, unused: no branch
+      // around the loads)
+#pragma unroll
+      for (int u = 0; u < PF; ++u) {
+        tile(y[u], t + u);
+        cols.load(min(t + u + PF, T.ct - 1), y[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PF - 1; ++u)
+      if (t + u < tb) tile(y[u], t + u);
+    if (h == 0)
+      for (; g < gs * GW + GW; ++g) part[g * PS] = make_double2(0.0, 0.0);   // empty groups
+  } else {
+#pragma unroll 1
+    for (int u = 0; u < GW; ++u) {
+      const int g = gs * GW + u;
+      const int tA = min(T.ct, g * T.tpg), tB = min(T.ct, g * T.tpg + T.tpg);
+      double gm = m0, gv = 0.0;
+#pragma unroll 1
+      for (int t = tA; t < tB; t += T.tps) {
+        double m, v;
+        dig_free_range<D>(cols, x, base, t, min(tB, t + T.tps), h, m, v);
+        f64_fold(gm, gv, m, v, false);
+      }
+      if (h == 0) part[g * PS] = make_double2(gm, gv);
+    }
+  }
+  __syncthreads();
+  if (gs != 0 || row0 >= nrows) return;
+  double Mt = 0.0, St = 0.0;
+  if (owner) {
+    double pm[kGroups], ps[kGroups];
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      pm[g] = part[g * PS].x;
+      ps[g] = part[g * PS].y;
+    }
+    f64_merge(pm, ps, Mt, St);
+  }
+  const bool o[1] = {owner}, lv[1] = {owner && live};
+  const double lo[1] = {lse_old}, l2[1] = {lm}, mt[1] = {Mt}, st[1] = {St};
+  const float ww[1] = {w};
+  finish_rows_r<kRowsDig, 1, 1, double, true>(L, P, s, si, rt0 + rg, o, lv, fast, M, lo, l2, ww, mt,
+                                              st, rhat);
 }
 
 // ----------------------------------------------- materialised-cost half-steps
@@ -2296,6 +2842,21 @@ __device__ __forceinline__ float export_potential(const float* gam, const float*
   return (gq + 0.5f * nrm) * (1.f / si.kappa);
 }
 
+// The same for a digit lane (never under guarded release): gam = log2 mass - lse,
+// as the half-step formed it, and the norm of the digits' sum.
+__device__ __forceinline__ float export_dig(const float* rec, const float* lm, const float* lse,
+                                            size_t e, int d, int dp, const SlotInfo& si) {
+  const double gq = reinterpret_cast<const double*>(lm)[e] - reinterpret_cast<const double*>(lse)[e];
+  if (gq == -(double)INFINITY) return 0.f;
+  const _Float16* r = reinterpret_cast<const _Float16*>(rec) + e * dp * 4;
+  double nrm = 0.0;
+  for (int k = 0; k < d; ++k) {
+    const double v = dig_coord(r, d, k);
+    nrm = fma(v, v, nrm);
+  }
+  return (float)potential_f64(gq, nrm, si.kappa64);
+}
+
 __global__ __launch_bounds__(256) void k_move(MoveArgs p) {
   const int s = blockIdx.y;
   const int A = p.compact ? min(p.A, p.ctrl->A_prev) : min(p.A, p.ctrl->A);
@@ -2314,9 +2875,12 @@ __global__ __launch_bounds__(256) void k_move(MoveArgs p) {
       const int padn = p.pad[side];
       float* out = side ? p.g : p.f;
       for (int q = c0 + threadIdx.x; q < min(lim, c0 + p.chunk); q += blockDim.x) {
-        const float v = q < cnt ? export_potential(p.src.gam[side][par], p.src.rec[side],
-                                                   (size_t)s * padn + q, p.dp, p.es, si)
-                                : 0.f;
+        const size_t e = (size_t)s * padn + q;
+        const float v = q >= cnt ? 0.f
+                        : si.dig ? export_dig(p.src.rec[side], p.src.lm[side], p.src.lse[side][par],
+                                              e, p.d, p.dp, si)
+                                 : export_potential(p.src.gam[side][par], p.src.rec[side], e, p.dp,
+                                                    p.es, si);
         out[(size_t)si.lane * lim + q] = v;
       }
     }
@@ -2353,9 +2917,9 @@ __global__ __launch_bounds__(256) void k_move(MoveArgs p) {
     if (blockIdx.x == 0) {
       // the row-block aggregates follow the lane (the next f-half reads the
       // g-half's ones as its bound)
-      for (int q = threadIdx.x; q < 4 * p.rbmax; q += blockDim.x) {
-        const int a = q / p.rbmax, e = q - a * p.rbmax;
-        p.dst.agg[a][(size_t)ns * p.rbmax + e] = p.src.agg[a][(size_t)s * p.rbmax + e];
+      for (int q = threadIdx.x; q < 4 * p.abmax; q += blockDim.x) {
+        const int a = q / p.abmax, e = q - a * p.abmax;
+        p.dst.agg[a][(size_t)ns * p.abmax + e] = p.src.agg[a][(size_t)s * p.abmax + e];
       }
       if (threadIdx.x == 0) {
         p.dst.slot[ns] = si;
@@ -2467,7 +3031,7 @@ __global__ __launch_bounds__(256) void k_vgate(Launch L, GuardArgs G) {
   if (!item_live(L, P, s, si, c_fin, c_A)) return;
   bool gate = true, checked = true;
   if (!P.final_audit) {
-    const LaneAgg g = lane_aggregate(P.agg_screen, s, L.rbmax, row_blocks(si.n, L.rows), false);
+    const LaneAgg g = lane_aggregate(P.agg_screen, s, L.abmax, agg_blocks(si.n, L.ashift), false);
     gate = !isfinite(g.sum) || !G.bound || guard_lower_bound(L, G, si, g.sum) <= (double)L.tol;
     checked = gate || P.verify_all;
   }
@@ -2794,7 +3358,8 @@ __global__ __launch_bounds__(256) void k_ingest_lanes(IngestArgs p) {
     si.lane = t; si.n = nt; si.m = mt; si.done = 0; si.passed = 0;
     si.kappa64 = 1.4426950408889634 / (double)e;
     si.kappa = (float)si.kappa64;
-    si.pad[0] = si.pad[1] = 0;
+    si.dig = 0;   // set by k_range
+    si.pad = 0;
     p.bank.slot[t] = si;
     Decision d;
     d.status = 1; d.depth = 0; d.res_row = NAN; d.res_col = NAN; d.new_slot = -1;
@@ -2813,8 +3378,77 @@ __global__ __launch_bounds__(256) void k_ingest_lanes(IngestArgs p) {
   }
   // no previous half-step: the first update of each side runs unanchored
   const float4 none = make_float4(0.f, INFINITY, -INFINITY, 1.f);
-  for (int q = threadIdx.x; q < p.rbmax; q += blockDim.x)
-    for (int k = 0; k < 4; ++k) p.bank.agg[k][(size_t)t * p.rbmax + q] = none;
+  for (int q = threadIdx.x; q < p.abmax; q += blockDim.x)
+    for (int k = 0; k < 4; ++k) p.bank.agg[k][(size_t)t * p.abmax + q] = none;
+}
+
+// Float64 state: whether a lane's exponents can be formed from digits. With R_x,
+// R_y the largest scaled norms, C = (R_x + R_y)^2 / 2 bounds kappa |x - y|^2; with
+// l the largest |log2 mass| plus log2 of the point count, every state keeps
+// osc(kappa f), osc(kappa g) <= C + l (each column of the coupling sums to its
+// mass, so f_i + g_j <= C_ij everywhere and some f_i + g_j >= -l), and <f, a>,
+// <g, b> never decrease while their sum stays below C: |kappa f|, |kappa g| <=
+// 2 (C + l) + 2 kappa max |g^0|. The column operands (potential minus half a
+// norm), the row anchors (a column operand's bound, plus l and the anchored
+// sums' range) and x~ . y~ then sum to at most `reach`. One block per lane.
+__global__ __launch_bounds__(256) void k_range(IngestArgs p) {
+  const int t = blockIdx.x;
+  if (p.ctrl->err_lane != 0x7fffffff) return;
+  const SlotInfo si = p.bank.slot[t];
+  const double sigma = sqrt(2.0 * si.kappa64);
+  const float* c = p.center + (size_t)t * p.d;
+  // per side the largest squared norm and whether a point is live; over both the
+  // largest coordinate, |log2 mass| and |kappa g^0| (NaN kept: it fails the test)
+  double norm[2] = {0.0, 0.0}, coord = 0.0, lmass = 0.0, prop = 0.0;
+  int bad = 0, live[2] = {0, 0};
+  for (int side = 0; side < 2; ++side) {
+    const int cnt = side ? si.m : si.n;
+    const int ld = side ? p.m_max : p.n_max;
+    const float* P = (side ? p.Y : p.X) + (size_t)t * ld * p.d;
+    const float* w = (side ? p.b : p.a) + (size_t)t * ld;
+    for (int q = threadIdx.x; q < cnt; q += blockDim.x) {
+      const float mass = w[q];
+      if (mass == 0.f) continue;
+      if (!(mass > 0.f) || !isfinite(mass)) { bad = 1; continue; }
+      live[side] = 1;
+      double nrm = 0.0;
+      for (int k = 0; k < p.d; ++k) {
+        const double v = fabs(sigma * ((double)P[(size_t)q * p.d + k] - (double)c[k]));
+        if (!(v <= kDigCoord)) bad = 1;
+        nrm = fma(v, v, nrm);
+      }
+      norm[side] = fmax(norm[side], nrm);
+      lmass = fmax(lmass, fabs(log2((double)mass)));
+      if (side == 1 && p.g0) {
+        const double g = fabs(si.kappa64 * (double)p.g0[(size_t)t * p.m_max + q]);
+        if (!(g <= kDigRange)) bad = 1;
+        prop = fmax(prop, g);
+      }
+    }
+  }
+  __shared__ double sh[4][256];
+  __shared__ int sh_flag[256];
+  sh[0][threadIdx.x] = norm[0];
+  sh[1][threadIdx.x] = norm[1];
+  sh[2][threadIdx.x] = lmass;
+  sh[3][threadIdx.x] = prop;
+  sh_flag[threadIdx.x] = bad | (live[0] << 1) | (live[1] << 2);
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) {
+      for (int k = 0; k < 4; ++k)
+        sh[k][threadIdx.x] = fmax(sh[k][threadIdx.x], sh[k][threadIdx.x + o]);
+      sh_flag[threadIdx.x] |= sh_flag[threadIdx.x + o];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  const double rx = sqrt(sh[0][0]), ry = sqrt(sh[1][0]);
+  const double l = sh[2][0] + log2((double)max(si.n, si.m)), g = sh[3][0];
+  const double C = 0.5 * (rx + ry) * (rx + ry), r2 = fmax(sh[0][0], sh[1][0]);
+  const double gam = 2.0 * (C + l) + 2.0 * g + 0.5 * r2;
+  const double reach = rx * ry + 2.0 * gam + l + 2.0 * (double)kFastRangePrecise;
+  p.bank.slot[t].dig = sh_flag[0] == 6 && reach <= kDigRange ? 1 : 0;
 }
 
 // Grid (chunks, W): points of both sides of lane t.
@@ -2853,6 +3487,39 @@ __global__ __launch_bounds__(256) void k_ingest_points(IngestArgs p, int chunk) 
             p.bank.gam[1][par][idx] = (float)kg0;
             p.bank.lse[1][par][idx] = (float)(lm - kg0);
           }
+        }
+        continue;
+      }
+      if (p.precise && si.dig) {
+        // digit record: piece by piece (h, l1, l2, l3 of every coordinate)
+        _Float16* rec = reinterpret_cast<_Float16*>(p.bank.rec[side]) + idx * p.dp * 4;
+        double nrm = 0.0;
+        for (int k = 0; k < p.d; ++k) {
+          double v = live ? sigma * ((double)P[((size_t)t * ld + q) * p.d + k] - (double)c[k]) : 0.0;
+          const double h = rint(v * 0x1p3) * 0x1p-3;
+          v -= h;
+          const double l1 = rint(v * 0x1p15) * 0x1p-15;
+          v -= l1;
+          const double l2 = rint(v * 0x1p27) * 0x1p-27;
+          v -= l2;
+          const double l3 = rint(v * 0x1p39) * 0x1p-39;
+          rec[k] = (_Float16)(float)h;
+          rec[p.d + k] = (_Float16)(float)l1;
+          rec[2 * p.d + k] = (_Float16)(float)(l2 * 0x1p12);
+          rec[3 * p.d + k] = (_Float16)(float)(l3 * 0x1p24);
+          const double u = dig_coord(rec, p.d, k);
+          nrm = fma(u, u, nrm);
+        }
+        for (int k = 4 * p.d; k < 4 * p.dp; ++k) rec[k] = (_Float16)0.f;
+        reinterpret_cast<double*>(p.bank.lm[side])[idx] = lm;
+        for (int par = 0; par < 2; ++par) {
+          double* lse = reinterpret_cast<double*>(p.bank.lse[side][par]);
+          f16x4* gam = reinterpret_cast<f16x4*>(p.bank.gam[side][par]);
+          // (side 0 has no state yet: the first f-half runs unanchored and
+          // writes it)
+          const double g = !live ? -(double)INFINITY : side == 0 ? 0.0 : kg0 - 0.5 * nrm;
+          gam[idx] = dig_gam(g);
+          lse[idx] = !live ? (double)INFINITY : side == 0 ? (double)NAN : lm - g;
         }
         continue;
       }
@@ -3015,6 +3682,20 @@ static hipError_t launch_f64_d(const Launch& a, int variant, int blocks, hipStre
   return hipGetLastError();
 }
 
+template <int D>
+static hipError_t launch_dig_d(const Launch& a, int variant, int blocks, hipStream_t st,
+                               hipEvent_t e0, hipEvent_t e1) {
+  // `blocks`: work items of 128 rows over both passes
+  switch (variant) {
+    case DIG_1X8: hipExtLaunchKernelGGL((k_update_dig<D, 1, 8>), dim3(4 * blocks), dim3(512), 0, st, e0, e1, 0, a); break;
+    case DIG_1X4: hipExtLaunchKernelGGL((k_update_dig<D, 1, 4>), dim3(4 * blocks), dim3(256), 0, st, e0, e1, 0, a); break;
+    case DIG_2X2: hipExtLaunchKernelGGL((k_update_dig<D, 2, 2>), dim3(2 * blocks), dim3(256), 0, st, e0, e1, 0, a); break;
+    case DIG_4X1: hipExtLaunchKernelGGL((k_update_dig<D, 4, 1>), dim3(blocks), dim3(256), 0, st, e0, e1, 0, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 }  // namespace ds
 
 // Entry points used by the host runtime (C++ linkage, same library).
@@ -3104,6 +3785,30 @@ hipError_t launch_update_f64(const Launch& a, int d, int variant, int blocks, hi
   }
 }
 
+hipError_t launch_update_dig(const Launch& a, int d, int variant, int blocks, hipStream_t st,
+                             hipEvent_t e0, hipEvent_t e1) {
+  if (blocks <= 0) return hipSuccess;
+  switch (d) {
+    case 1: return launch_dig_d<1>(a, variant, blocks, st, e0, e1);
+    case 2: return launch_dig_d<2>(a, variant, blocks, st, e0, e1);
+    case 3: return launch_dig_d<3>(a, variant, blocks, st, e0, e1);
+    case 4: return launch_dig_d<4>(a, variant, blocks, st, e0, e1);
+    case 5: return launch_dig_d<5>(a, variant, blocks, st, e0, e1);
+    case 6: return launch_dig_d<6>(a, variant, blocks, st, e0, e1);
+    case 7: return launch_dig_d<7>(a, variant, blocks, st, e0, e1);
+    case 8: return launch_dig_d<8>(a, variant, blocks, st, e0, e1);
+    case 9: return launch_dig_d<9>(a, variant, blocks, st, e0, e1);
+    case 10: return launch_dig_d<10>(a, variant, blocks, st, e0, e1);
+    case 11: return launch_dig_d<11>(a, variant, blocks, st, e0, e1);
+    case 12: return launch_dig_d<12>(a, variant, blocks, st, e0, e1);
+    case 13: return launch_dig_d<13>(a, variant, blocks, st, e0, e1);
+    case 14: return launch_dig_d<14>(a, variant, blocks, st, e0, e1);
+    case 15: return launch_dig_d<15>(a, variant, blocks, st, e0, e1);
+    case 16: return launch_dig_d<16>(a, variant, blocks, st, e0, e1);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_update_mat(const Launch& a, int blocks, hipStream_t st, hipEvent_t e0,
                              hipEvent_t e1) {
   if (blocks <= 0) return hipSuccess;
@@ -3182,6 +3887,7 @@ hipError_t launch_ingest(const IngestArgs& a, int maxpad, hipStream_t st) {
   int kw = 1;
   while (kw < a.d && kw < 64) kw *= 2;
   hipLaunchKernelGGL(k_centre, dim3((a.d + kw - 1) / kw, a.W), dim3(256), 0, st, a, kw);
+  if (a.digits) hipLaunchKernelGGL(k_range, dim3(a.W), dim3(256), 0, st, a);
   const int chunk = 1024;
   const int chunks = (maxpad + chunk - 1) / chunk;
   hipLaunchKernelGGL(k_ingest_points, dim3(chunks, a.W), dim3(256), 0, st, a, chunk);

@@ -1,0 +1,119 @@
+"""The float64-state half-step formed from float16 digits on the matrix cores
+(k_update_dig): every dimension it serves, at point counts around its 32-row and
+32-column tiles, its 128-row items and its column groups, against the float64
+oracle; against the float64 vector kernels, which guarded release runs; and
+windows that mix its lanes with lanes whose exponents are out of the digits'
+range, which keep the vector kernels.
+
+Tolerances: potentials are float32 outputs (half an ulp, 6e-8 of the largest) of
+a state whose exponents are rounded once to float32, as on the vector path, so
+1e-6 of the largest potential covers both with room; residuals keep the 1e-5
+absolute bar of the parity tests."""
+
+import numpy as np
+import pytest
+
+from paper_2607_24741_amd import workloads as wl
+from tests.gpu_support import compare, log, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+F_GUARD = 64
+
+
+def _window(W, n, m, d, seed, spread=1.0, ragged=True):
+    """W lanes of Gaussian clouds with Dirichlet masses (a few of them zero)."""
+    rng = np.random.default_rng([seed, n, m, d])
+    N = np.full(W, n, np.int32)
+    M = np.full(W, m, np.int32)
+    if ragged and W > 1:
+        N[1:] = rng.integers(max(1, n // 2), n + 1, W - 1)
+        M[1:] = rng.integers(max(1, m // 2), m + 1, W - 1)
+    X = np.full((W, n, d), np.nan, np.float32)
+    Y = np.full((W, m, d), np.nan, np.float32)
+    A = np.full((W, n), np.nan, np.float32)
+    B = np.full((W, m), np.nan, np.float32)
+    for t in range(W):
+        X[t, :N[t]] = spread * rng.standard_normal((N[t], d))
+        Y[t, :M[t]] = spread * (rng.standard_normal((M[t], d)) + 0.3)
+        a, b = rng.gamma(1.0, size=N[t]) + 1e-3, rng.gamma(1.0, size=M[t]) + 1e-3
+        if N[t] > 3:
+            a[N[t] // 2] = 0.0
+        A[t, :N[t]] = a / a.sum()
+        B[t, :M[t]] = b / b.sum()
+    E = (d * spread * spread * np.exp(rng.uniform(np.log(0.05), np.log(0.4), W))).astype(np.float32)
+    return wl.Workload(name="digits", X=X, Y=Y, a=A, b=B, eps=E, n=N, m=M, tol=1e-4, max_iter=40)
+
+
+def _close(got, ref, w, lanes=None, bar=1e-6):
+    for t in range(w.W) if lanes is None else lanes:
+        scale = max(np.abs(ref["f"][t]).max(), np.abs(ref["g"][t]).max(), float(w.eps[t]))
+        err = max(np.abs(got["f"][t] - ref["f"][t]).max(), np.abs(got["g"][t] - ref["g"][t]).max())
+        assert err <= bar * scale, (t, err / scale)
+
+
+@pytest.mark.parametrize("d", range(1, 17))
+def test_every_dimension_around_the_tiles(d):
+    # 33 x 31: a second row tile of one row, a partial column tile; 130 x 257: a
+    # second item, eight groups and a remainder; 1 x 65: one row
+    for n, m in ((33, 31), (130, 257), (1, 65)):
+        w = _window(3, n, m, d, seed=11)
+        log(f"[case] digits d={d} n={n} m={m}")
+        got = run_gpu(w, w.tol, max_iter=w.max_iter)
+        rep = compare(w, got, run_oracle(w, w.tol, max_iter=w.max_iter), w.tol,
+                      max_iter=w.max_iter)
+        assert rep["max_pot_err"] <= 1e-6
+        # the vector kernels at the same fixed work (guarded release runs them)
+        kw = dict(max_iter=5)
+        a, b = run_gpu(w, 1e-9, **kw), run_gpu(w, 1e-9, flags=F_GUARD, **kw)
+        _close(a, b, w)
+
+
+@pytest.mark.parametrize("n,m,d", [(1025, 1023, 3), (700, 2100, 2), (1100, 520, 8), (515, 640, 16)])
+def test_layouts_give_the_same_bits(n, m, d):
+    # one lane alone, few and many lanes: every block layout the widths choose
+    big = _window(64, n, m, d, seed=5)
+    log(f"[case] digits layouts n={n} m={m} d={d}")
+    ref = run_gpu(big, 1e-9, max_iter=6)
+    for W, streams in ((1, 1), (3, 1), (20, 1), (64, 1)):
+        part = wl.Workload(name="part", X=big.X[:W], Y=big.Y[:W], a=big.a[:W], b=big.b[:W],
+                           eps=big.eps[:W], n=big.n[:W], m=big.m[:W], tol=1e-9, max_iter=6)
+        got = run_gpu(part, 1e-9, max_iter=6, streams=streams)
+        for k in ("f", "g", "residual"):
+            assert np.array_equal(got[k], ref[k][:W]), (W, streams, k)
+
+
+def test_uniform_layouts_give_the_same_bits():
+    big = _window(48, 513, 700, 5, seed=6, ragged=False)
+    log("[case] digits uniform layouts")
+    ref = run_gpu(big, 1e-9, max_iter=6)
+    for W in (1, 9, 30):
+        part = wl.Workload(name="part", X=big.X[:W], Y=big.Y[:W], a=big.a[:W], b=big.b[:W],
+                           eps=big.eps[:W], n=big.n[:W], m=big.m[:W], tol=1e-9, max_iter=6)
+        got = run_gpu(part, 1e-9, max_iter=6)
+        for k in ("f", "g", "residual"):
+            assert np.array_equal(got[k], ref[k][:W]), (W, k)
+
+
+@pytest.mark.parametrize("ragged", [False, True])
+def test_lanes_out_of_range_keep_the_vector_kernels(ragged):
+    # lane 1: exponents far beyond the digits' range (tiny eps); lane 3: a shift
+    # that leaves coordinates too large for them; both beside ordinary lanes
+    w = _window(5, 300, 260, 3, seed=9, ragged=ragged)
+    w.eps[1] = 2e-5
+    w.X[3] *= 40.0
+    w.Y[3] *= 40.0
+    log(f"[case] digits mixed window ragged={ragged}")
+    kw = dict(max_iter=25)
+    got = run_gpu(w, 1e-9, **kw)
+    _close(got, run_oracle(w, 1e-9, max_iter=25), w)
+    _close(got, run_gpu(w, 1e-9, flags=F_GUARD, **kw), w)
+    # the vector lanes: the same bits as alone
+    for t in (1, 3):
+        one = wl.Workload(name="one", X=w.X[t:t + 1], Y=w.Y[t:t + 1], a=w.a[t:t + 1], b=w.b[t:t + 1],
+                          eps=w.eps[t:t + 1], n=w.n[t:t + 1], m=w.m[t:t + 1], tol=1e-9, max_iter=25)
+        alone = run_gpu(one, 1e-9, **kw)
+        assert np.array_equal(alone["f"][0], got["f"][t])
+    # retirement in such a window: every lane stops where the oracle stops
+    got = run_gpu(w, 1e-2, max_iter=400)
+    compare(w, got, run_oracle(w, 1e-2, max_iter=400), 1e-2, max_iter=400)
