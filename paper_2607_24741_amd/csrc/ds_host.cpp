@@ -126,7 +126,9 @@ ds::Layout plan(const ds_problem* pr, const ds_options* op, void* ws) {
     B.slot = c.take<ds::SlotInfo>(W);
     for (int role = 0; role < 2; ++role) B.ord[role] = c.take<int>(W);
     B.dec = c.take<ds::Decision>(W);
-    for (int k = 0; k < 4; ++k) B.agg[k] = c.take<float4>(W * (size_t)L.abmax);
+    // (the same room with and without guarded release)
+    for (int k = 0; k < 4; ++k)
+      B.agg[k] = c.take<float4>(W * (size_t)(L.rbmax * (L.es == 2 ? L.rows / ds::kRowsDig : 1)));
   }
   L.center = c.take<float>(W * (size_t)L.d);
   L.vcnt = c.take<int>(W);
