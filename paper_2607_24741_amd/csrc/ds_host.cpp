@@ -316,6 +316,7 @@ struct PartOut {
   int launched = 0, compactions = 0, n_timed = 0;
   int64_t bytes_compacted = 0;
   bool timing = false;
+  bool resident = false;     // some cycles ran in resident slices
   std::vector<Timed> timed;
   double ms_update = 0.0, ms_compact = 0.0;
   std::vector<int32_t> nchk;
@@ -569,6 +570,29 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
   int64_t bytes_compacted = 0;  // upper bound: survivors x per-lane state bytes
   const int64_t lane_bytes = (int64_t)(L.pad[0] + L.pad[1]) * (L.dp + 5) * 4 * L.es +
                              (int64_t)(sizeof(SlotInfo) + sizeof(Decision));
+  // Small lanes: slices of many cycles in one launch, a block per lane
+  // (k_resident), as long as that is the faster way to run the lanes that are
+  // left. Per cycle a resident lane takes res_fix plus its 32 x 32 tiles on one
+  // CU; the per-half launches take a fixed time plus all lanes' tiles over the
+  // chip. Both leave the same state, so the choice is taken anew at every slice.
+  const bool may_reside = active && precise && n_dig == W && !shadow && !guard && !tm.on;
+  size_t lds_top = 0;   // (of every lane's own shape: a small one may take more than a larger one)
+  double tiles_top = 0.0, tiles_sum = 0.0;
+  for (int t = 0; t < W; ++t) {
+    const double tl = (double)((lanes[t].n + 31) / 32) * (double)((lanes[t].m + 31) / 32);
+    if (may_reside) lds_top = std::max(lds_top, resident_lds_bytes(d, lanes[t].n, lanes[t].m));
+    tiles_top = std::max(tiles_top, tl);
+    tiles_sum += tl;
+  }
+  const bool reside_fits = may_reside && lds_top <= kResidentLds;
+  // us per cycle of `A` lanes of this sub-batch (the others like it)
+  auto reside_us = [&](int A) -> double {
+    const int rounds = (A * parts + 255) / 256;
+    return rounds * (kResidentFixUs + 2.0 * tiles_top * resident_tile_us(d));
+  };
+  auto launches_us = [&](int A) -> double {
+    return kLaunchesFixUs + 2.0 * tiles_sum / W * A * parts * launches_tile_us(d) / 256.0;
+  };
   for (int k = 1; k <= max_iter; ++k) {
     // bounded run-ahead: wait for the device only when too far behind
     // (block 0 of every update launch publishes the launch's sequence
@@ -629,6 +653,34 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
       compactions++;
     }
     if (A <= 0) break;
+    if (reside_fits && reside_us(std::min(A, s_act)) < launches_us(std::min(A, s_act))) {
+      ResidentArgs ra;
+      std::memset(&ra, 0, sizeof(ra));
+      const Bank& B = L.bank[bank];
+      for (int side = 0; side < 2; ++side) {
+        ra.rec[side] = B.rec[side];
+        ra.lm[side] = B.lm[side];
+        for (int par = 0; par < 2; ++par) {
+          ra.lse[side][par] = B.lse[side][par];
+          ra.gam[side][par] = B.gam[side][par];
+        }
+        ra.w[side] = side ? pr->b : pr->a;
+        ra.w_ld[side] = side ? pr->m_max : pr->n_max;
+        ra.pad[side] = L.pad[side];
+      }
+      ra.agg_g = B.agg[AGG_G];
+      // slices of a few milliseconds: long against the launch and the wait for it,
+      // short enough that retired lanes are compacted away and the choice renewed
+      const int span = std::max(16, std::min(1024, (int)(4000.0 / reside_us(std::min(A, s_act)))));
+      ra.k0 = k;
+      ra.k1 = std::min(max_iter, k + span - 1);
+      ra.ae = ae;
+      HIP_TRY(launch_resident(make_launch(), ra, d, A, lds_top, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      k = launched = ra.k1;
+      out.resident = true;
+      continue;
+    }
     const int pk = k & 1, pk1 = (k - 1) & 1;
     const bool sample = (k % kSampleEvery) == 0;
     const bool audit_prev = (k - 1 >= 1) && ((k - 1) % ae == 0);
@@ -961,7 +1013,15 @@ ds_err ds_solve(const ds_problem* pr, const ds_options* op, const ds_result* res
       }
       retire_events += o.ctrl.retire_events;
       for (float v : o.disc) S.screen_discrepancy = std::max(S.screen_discrepancy, (double)v);
-      launched = std::max(launched, o.launched);
+      // (a resident slice's lanes stop by themselves: no cycle past the deepest
+      // lane's own was run)
+      int pl = o.launched;
+      if (o.resident && o.ctrl.finished) {
+        int plmax = 0;
+        for (size_t u = 0; u < o.lanes.size(); ++u) plmax = std::max(plmax, depth[lo + (int)u]);
+        pl = std::min(pl, plmax + 1);
+      }
+      launched = std::max(launched, pl);
       finished_all &= o.ctrl.finished ? 1 : 0;
       S.screen_positive += o.ctrl.screen_pos;
       S.check_failures += o.ctrl.check_fail;

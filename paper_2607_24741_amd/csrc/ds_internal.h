@@ -331,6 +331,18 @@ struct GuardArgs {
                           // state); 0: verify every audited lane
 };
 
+// k_resident: cycles k0..k1 of every lane, a block each
+struct ResidentArgs {
+  const float* rec[2];
+  const float* lm[2];
+  float* lse[2][2];
+  float* gam[2][2];
+  float4* agg_g;             // the g-half's aggregates (see AGG_G)
+  const float* w[2];         // caller masses
+  int w_ld[2], pad[2];
+  int k0, k1, ae;            // cycles of this launch, audit spacing
+};
+
 struct ScanArgs {          // compaction map over the slots of the current bank
   SlotInfo* slot;
   Decision* dec;
@@ -404,6 +416,25 @@ hipError_t launch_update_dig(const Launch& a, int d, int variant, int blocks, hi
 // work items over both passes
 hipError_t launch_update_mfma_k(const Launch& a, int blocks, hipStream_t st,
                                 hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// LDS a resident lane may use (a CU's), and what a lane of n x m points takes
+constexpr size_t kResidentLds = 163840;
+size_t resident_lds_bytes(int d, int n, int m);
+// The choice between resident slices and per-half launches (see solve_part): us
+// per cycle, fixed and per 32 x 32 tile of both halves. Measured: a resident lane of
+// 2 x 2 tiles (toy, d = 2) 7.0 us per cycle against 13, of 16 x 16 tiles 37 us at
+// d = 8 and 44 at d = 16 on up to 256 lanes; per-half launches 13 to 14 us for a few
+// lanes, 28 / 48 / 76 us for 64 / 128 / 256 telemetry lanes (d = 16, 16 x 16
+// tiles), 39 us for 64 mixture lanes (d = 8, 32 x 32), 323 us for 64 LiDAR lanes
+// (d = 3, 128 x 128)
+constexpr double kResidentFixUs = 7.0;
+constexpr double resident_tile_us(int d) { return d <= 4 ? 0.045 : d <= 8 ? 0.058 : 0.072; }
+constexpr double kLaunchesFixUs = 13.5;
+constexpr double launches_tile_us(int d) {
+  return d <= 4 ? 0.036 : d <= 8 ? 0.045 : d <= 12 ? 0.08 : 0.115;
+}
+// cycles k0..k1 of A lanes, all with digit records, none taking more than `lds` bytes
+hipError_t launch_resident(const Launch& a, const ResidentArgs& r, int d, int A, size_t lds,
+                           hipStream_t st);
 hipError_t launch_update_mat(const Launch& a, int blocks, hipStream_t st, hipEvent_t e0 = nullptr,
                              hipEvent_t e1 = nullptr);
 

@@ -331,6 +331,13 @@ __device__ __forceinline__ f16x4 dig_gam(double g) {
   k.w = (_Float16)(float)k4;
   return k;
 }
+// Point of a 32-point tile that lane `lane` (and lane ^ 32) holds, as a column and
+// as a row of the digit kernels: the matrix cores then leave the even columns in
+// the lanes below 32 and the odd ones in the others, in order.
+__device__ __forceinline__ int dig_point(int lane) {
+  const int r = lane & 31;
+  return 2 * (4 * (r >> 3) + (r & 3)) + ((r >> 2) & 1);
+}
 // coordinate k of a digit record of d coordinates (exact in float64)
 __device__ __forceinline__ double dig_coord(const _Float16* r, int d, int k) {
   return ((double)(float)r[k] + (double)(float)r[d + k]) +
@@ -350,7 +357,8 @@ __device__ __forceinline__ double log2_t(double x) { return log2(x); }
 __device__ __forceinline__ float exp2_t(float x) { return ex2(x); }
 __device__ __forceinline__ double exp2_t(double x) { return exp2(x); }
 
-// DIG: digit lanes (T = double): the new column operand is stored as digits.
+// DIG: digit lanes (T = double, 32 rows): lane l < 32 owns row dig_point(l), and
+// the new column operand is stored as digits.
 template <int UNIT, int NU, int R, typename T, bool DIG = false>
 __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotInfo& si, int rb0,
                               const bool (&owner)[R], const bool (&live)[R], bool fast, float Mf,
@@ -427,7 +435,7 @@ __device__ void finish_rows_r(const Launch& L, const Pass& P, int s, const SlotI
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (!owner[r]) continue;
-        const size_t idx = (size_t)s * P.padr + rb0 * UNIT + 64 * r + lane;
+        const size_t idx = (size_t)s * P.padr + rb0 * UNIT + (DIG ? dig_point(lane) : 64 * r + lane);
         reinterpret_cast<T*>(P.lse_out)[idx] = lse_new[r];
         if (DIG) reinterpret_cast<f16x4*>(P.gam_out)[idx] = dig_gam((double)gam_new[r]);
         else reinterpret_cast<T*>(P.gam_out)[idx] = gam_new[r];
@@ -2009,14 +2017,34 @@ struct DigRow {
     if constexpr (C + 1 < NC) fill4<LEVEL, C + 1>(f, h);
     else if constexpr (LEVEL + 1 < 4) fill4<LEVEL + 1, 0>(f, h);
   }
+  // the record's 16-byte pieces q (eight slots) from rec + q * 16 (memory), or
+  // from a digit image: chunk q / 2, half q % 2 of lane r
+  static constexpr int NV = (4 * D + 7) / 8;
   __device__ __forceinline__ void load(const _Float16* rec, int h) {
+    f16x8 v[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = reinterpret_cast<const f16x8*>(rec)[q];
+    form(v, h);
+  }
+  __device__ __forceinline__ void load_image(const char* tile, int lane) {
+    f16x8 v[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q)
+      v[q] = *reinterpret_cast<const f16x8*>(tile + 1024 * (q / 2) + 16 * ((lane & 31) + 32 * (q % 2)));
+    form(v, lane >> 5);
+  }
+  __device__ __forceinline__ void form(const f16x8 (&v)[NV], int h) {
     const _Float16 up = (_Float16)4096.f, down = (_Float16)0x1p-12f;
     if constexpr (D % 4 == 0) {
       f16x4 f[6][D / 4];
 #pragma unroll
       for (int k = 0; k < D / 4; ++k) {
-        const f16x4* v = reinterpret_cast<const f16x4*>(rec) + k;
-        const f16x4 a = v[0], b = v[D / 4], c = v[2 * (D / 4)], e = v[3 * (D / 4)];
+        auto quad = [&](int i) {   // slots 4 i .. 4 i + 3
+          return (i & 1) ? __builtin_shufflevector(v[i / 2], v[i / 2], 4, 5, 6, 7)
+                         : __builtin_shufflevector(v[i / 2], v[i / 2], 0, 1, 2, 3);
+        };
+        const f16x4 a = quad(k), b = quad(D / 4 + k), c = quad(2 * (D / 4) + k),
+                    e = quad(3 * (D / 4) + k);
         f[Dig<D>::H][k] = a;
         f[Dig<D>::L1][k] = b;
         f[Dig<D>::L2][k] = c;
@@ -2026,10 +2054,6 @@ struct DigRow {
       }
       fill4<0, 0>(f, h);
     } else {
-      constexpr int NV = Dig<D>::REC / 8;
-      f16x8 v[NV];
-#pragma unroll
-      for (int q = 0; q < NV; ++q) v[q] = reinterpret_cast<const f16x8*>(rec)[q];
       _Float16 f[6][D];
 #pragma unroll
       for (int k = 0; k < D; ++k) {
@@ -2083,8 +2107,7 @@ struct DigCols {
   const char* gam;    // and its operands
   bool hi;
   __device__ __forceinline__ DigCols(const void* rec_lane, const void* gam_lane, int lane) {
-    const int r = lane & 31;
-    const int c = 2 * (4 * (r >> 3) + (r & 3)) + ((r >> 2) & 1);   // tile row r's column
+    const int c = dig_point(lane);
     hi = lane >= 32;
     rec = reinterpret_cast<const char*>(rec_lane) + (size_t)c * RB + (hi ? 16 : 0);
     gam = reinterpret_cast<const char*>(gam_lane) + (size_t)c * 8;
@@ -2173,9 +2196,9 @@ __device__ __forceinline__ float dig_tile_max(const f16x8 (&y)[Dig<D>::NC], cons
 // anchor from the previous cycle: a first sweep finds the row's largest exponent
 // above `base` (the range's own anchor), a second one sums. Leaves the row
 // anchored at `base`.
-template <int D>
-__device__ __forceinline__ void dig_free_range(const DigCols<D>& cols, DigRow<D>& x, double base,
-                                               int t0, int t1, int h, double& m, double& s) {
+template <int D, class Cols>
+__device__ __forceinline__ void dig_free_range(const Cols& cols, DigRow<D>& x, double base, int t0,
+                                               int t1, int h, double& m, double& s) {
   f16x8 y[Dig<D>::NC];
   float mx = -INFINITY;
 #pragma unroll 1
@@ -2261,7 +2284,7 @@ void k_update_dig(Launch L) {
   const int rg = wave % RG, gs = wave / RG;
   const int row0 = (rt0 + rg) * kRowsDig;
   // every load of the item goes out before the block waits on any of them
-  const int i = row0 + (lane & 31);
+  const int i = row0 + dig_point(lane);
   const size_t ridx = (size_t)s * P.padr + i;
   const double lse_old = reinterpret_cast<const double*>(P.lse_in)[ridx];
   const bool owner = gs == 0 && lane < kRowsDig && i < nrows;
@@ -2350,21 +2373,321 @@ void k_update_dig(Launch L) {
   }
   __syncthreads();
   if (gs != 0 || row0 >= nrows) return;
+  // the groups in order
   double Mt = 0.0, St = 0.0;
-  if (owner) {
-    double pm[kGroups], ps[kGroups];
+  if (owner && fast) {
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-      pm[g] = part[g * PS].x;
-      ps[g] = part[g * PS].y;
-    }
-    f64_merge(pm, ps, Mt, St);
+    for (int g = 0; g < kGroups; ++g) St += part[g * PS].y;
+  } else if (owner) {
+    Mt = -(double)INFINITY;
+#pragma unroll 1
+    for (int g = 0; g < kGroups; ++g) f64_fold(Mt, St, part[g * PS].x, part[g * PS].y, false);
+    if (Mt == -(double)INFINITY) Mt = 0.0;
   }
   const bool o[1] = {owner}, lv[1] = {owner && live};
   const double lo[1] = {lse_old}, l2[1] = {lm}, mt[1] = {Mt}, st[1] = {St};
   const float ww[1] = {w};
   finish_rows_r<kRowsDig, 1, 1, double, true>(L, P, s, si, rt0 + rg, o, lv, fast, M, lo, l2, ww, mt,
                                               st, rhat);
+}
+
+// ------------------------------------------------------ resident small lanes
+// Many cycles of one lane in one block, for lanes that fit in LDS: no launch,
+// placement or hand-off between the halves of a cycle, and nothing stored to
+// memory inside the loop (a barrier would wait for it). The digits of both sides
+// stay in LDS for the whole launch, in the order in which the matrix cores take
+// them; column operands, lse and aggregates are exchanged through LDS; masses are
+// read from memory. A launch runs cycles k0..k1 of every lane and leaves the
+// state, by parity, and the aggregates as the per-half launches do, so that
+// either can continue.
+//
+// Eight waves. With five or more row tiles a wave takes whole tiles; with fewer,
+// the waves of a tile share its column groups and the partials are merged
+// through LDS. Per tile and group the arithmetic and its order are those of
+// k_update_dig: the same bits.
+//
+// What bounds it: the sweeps of one CU (about 410 cycles per 1024 terms and SIMD
+// at two waves per SIMD, see k_update_dig) plus the barriers and finishes.
+
+// Digit image of a side in LDS: tile t, chunk c as 64 lanes x 16 bytes.
+template <int D>
+struct DigLds {
+  static constexpr int NC = Dig<D>::NC;
+  static constexpr int NI = (D + 3) / 4;     // chunks that hold digits
+  static constexpr int TB = NI * 1024;       // image bytes per tile
+  const char* img;   // this lane's 16 bytes of tile 0, chunk 0
+  const char* gam;   // this lane's column's operand, tile 0
+  bool hi;
+  __device__ __forceinline__ DigLds(const char* image, const char* operands, int lane) {
+    img = image + 16 * lane;
+    gam = operands + 8 * dig_point(lane);
+    hi = lane >= 32;
+  }
+  __device__ __forceinline__ void load(int t, f16x8 (&y)[NC]) const {
+#pragma unroll
+    for (int c = 0; c < NI; ++c)
+      y[c] = *reinterpret_cast<const f16x8*>(img + t * TB + 1024 * c);
+    const f16x4 k = *reinterpret_cast<const f16x4*>(gam + t * (kColTile * 8));
+    if constexpr (D % 4 == 0) {
+      y[NC - 1] = __builtin_shufflevector(k, DigCols<D>::weights(), 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      // the operand's slots 4 D .. + 3, in the last chunk beside digits
+      typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+      constexpr int hg = (D % 4) / 2, pg = D % 2;
+      u32x4 v = __builtin_bit_cast(u32x4, y[NC - 1]);
+      const u32x2 q = __builtin_bit_cast(u32x2, k);
+      const bool mine = hi == (hg == 1);
+      v[2 * pg] = mine ? q.x : v[2 * pg];
+      v[2 * pg + 1] = mine ? q.y : v[2 * pg + 1];
+      y[NC - 1] = __builtin_bit_cast(f16x8, v);
+    }
+  }
+};
+// LDS of a resident lane of n x m points: images, operands and lse (x by parity,
+// y), aggregates (f, g, check), and the partials of shared row tiles
+template <int D>
+__host__ __device__ constexpr size_t resident_lds(int n, int m) {
+  const size_t tx = (n + 31) / 32, ty = (m + 31) / 32;
+  const size_t part = (tx <= 4 || ty <= 4) ? (size_t)kGroups * 4 * kRowsDig * sizeof(double2) : 0;
+  return (tx + ty) * DigLds<D>::TB + (2 * tx + ty) * 512 + (tx + 2 * ty) * 16 + part;
+}
+
+constexpr int kResidentWaves = 8;
+template <int D>
+__global__ __launch_bounds__(64 * kResidentWaves, 2) void k_resident(Launch L, ResidentArgs R) {
+  constexpr int NC = Dig<D>::NC, NI = DigLds<D>::NI, TB = DigLds<D>::TB;
+  constexpr int NW = kResidentWaves;
+  static_assert(kGroups == 8 && NW == 8, "shares of a row tile");
+  extern __shared__ __align__(16) char lds[];
+  const int s = blockIdx.x;
+  if (s >= L.ctrl->A || L.ctrl->finished) return;
+  const SlotInfo si = L.slot[s];
+  if (si.done) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5;
+  const int tx = (si.n + kColTile - 1) / kColTile, ty = (si.m + kColTile - 1) / kColTile;
+  char* const imgx = lds;
+  char* const imgy = imgx + tx * TB;
+  char* const opx = imgy + ty * TB;            // [parity][tile] 256 bytes
+  char* const opy = opx + 2 * tx * 256;
+  char* const lsx = opy + ty * 256;            // [parity][tile] 256 bytes
+  char* const lsy = lsx + 2 * tx * 256;
+  float4* const agg_f = reinterpret_cast<float4*>(lsy + ty * 256);
+  float4* const agg_g = agg_f + tx;
+  float4* const agg_c = agg_g + ty;
+  double2* const sh_part = reinterpret_cast<double2*>(agg_c + ty);   // shared row tiles: at most 4
+  {
+    const int par = (R.k0 - 1) & 1;   // the state before cycle k0
+    for (int side = 0; side < 2; ++side) {
+      const int nt = side ? ty : tx;
+      const size_t p0 = (size_t)s * R.pad[side];
+      const char* rec = reinterpret_cast<const char*>(R.rec[side]) + p0 * DigCols<D>::RB;
+      char* const img = side ? imgy : imgx;
+      for (int e = tid; e < nt * NI * 64; e += 64 * NW) {
+        const int l = e & 63, c = (e >> 6) % NI, t = (e >> 6) / NI;
+        const char* r = rec + (size_t)(t * kColTile + dig_point(l)) * DigCols<D>::RB;
+        f16x4 p[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int s4 = 4 * c + 2 * (l >> 5) + q;
+          const _Float16 z = (_Float16)0.f;
+          p[q] = s4 < D ? *reinterpret_cast<const f16x4*>(r + 8 * s4)
+                        : (s4 == D + 1 && !Dig<D>::SPLAT) ? DigCols<D>::weights() : f16x4{z, z, z, z};
+        }
+        *reinterpret_cast<f16x8*>(img + (size_t)(t * NI + c) * 1024 + 16 * l) =
+            __builtin_shufflevector(p[0], p[1], 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+      // operands and lse, padding included (dead points); x: both parities (the
+      // other one's points are written before they are read)
+      const f16x4* gam = reinterpret_cast<const f16x4*>(
+          reinterpret_cast<const double*>(R.gam[side][par]) + p0);
+      const double* lse = reinterpret_cast<const double*>(R.lse[side][par]) + p0;
+      f16x4* const op = reinterpret_cast<f16x4*>(side ? opy : opx);
+      double* const ls = reinterpret_cast<double*>(side ? lsy : lsx);
+      for (int i = tid; i < nt * kColTile; i += 64 * NW) {
+        op[i] = gam[i];
+        ls[i] = lse[i];
+        if (side == 0) {
+          op[nt * kColTile + i] = gam[i];
+          ls[nt * kColTile + i] = lse[i];
+        }
+      }
+    }
+    for (int q = tid; q < ty; q += 64 * NW) agg_g[q] = R.agg_g[(size_t)s * L.abmax + q];
+  }
+  __syncthreads();
+
+  enum { F_HALF = 0, CHECK = 1, G_HALF = 2 };
+  int ph = F_HALF, k = R.k0;
+  float rhat = NAN;
+#pragma unroll 1
+  while (true) {
+    const int role = ph == F_HALF ? 0 : 1;
+    const int pk = k & 1, pk1 = pk ^ 1;
+    const bool upd = ph != CHECK;
+    const int nrows = role ? si.m : si.n, ncols = role ? si.n : si.m, rts = role ? ty : tx;
+    // state of the row side (in LDS, so without a lane offset), columns
+    const double* const lse_in = reinterpret_cast<const double*>(role ? lsy : lsx + pk1 * tx * 256);
+    Pass P;
+    P.role = role;
+    P.kind = upd ? KIND_UPDATE : KIND_VERIFY;
+    P.decide = 0;
+    P.final_audit = 0;
+    P.depth = k - 1;
+    P.padr = 0;
+    P.lse_out = reinterpret_cast<float*>(role ? lsy : lsx + pk * tx * 256);
+    P.gam_out = reinterpret_cast<float*>(role ? opy : opx + pk * tx * 256);
+    P.agg_out = ph == F_HALF ? agg_f : ph == CHECK ? agg_c : agg_g;
+    P.agg_bound = ph == F_HALF ? agg_g : agg_f;
+    const double* const lm_row = reinterpret_cast<const double*>(R.lm[role]) + (size_t)s * R.pad[role];
+    const float* const w_row = R.w[role] + (size_t)si.lane * R.w_ld[role];
+    const char* const img_row = role ? imgy : imgx;
+    bool fast = false;
+    float M = 0.f;
+    if (upd) update_facts(L, P, 0, ncols, fast, M, kFastRangePrecise);   // (this lane's own)
+    const F64Tiling T(ncols);
+    const DigLds<D> cols(role ? imgx : imgy, role ? opx + (ph == G_HALF ? pk : pk1) * tx * 256 : opy,
+                         lane);
+    const int shares = rts >= 5 ? 1 : rts >= 3 ? 2 : rts == 2 ? 4 : 8;
+    const int across = NW / shares;    // row tiles side by side
+    const int gs = wave / across, GW = kGroups / shares;
+    const double m0 = fast ? 0.0 : -(double)INFINITY;
+#pragma unroll 1
+    for (int rt = wave % across; rt < (shares == 1 ? rts : across); rt += across) {
+      const bool any = rt < rts;
+      const int i = (any ? rt : 0) * kRowsDig + dig_point(lane);
+      const bool owner = any && gs == 0 && lane < kRowsDig && i < nrows;
+      double lm = 0.0;
+      float w = 0.f;
+      if (owner) {
+        lm = lm_row[i];
+        w = w_row[i];
+      }
+      const double lse_old = lse_in[i];
+      DigRow<D> x;
+      x.load_image(img_row + (any ? rt : 0) * TB, lane);
+      const bool live = any && i < nrows && lse_old != (double)INFINITY;
+      const double base = !live ? 0.0 : !upd ? lse_old : fast ? lse_old + (double)M : 0.0;
+      x.anchor(base, h);
+      double Mt = m0, St = 0.0;   // the row's groups in order
+      double2* const part = sh_part + (rt & 3) * kRowsDig + (lane & 31);
+      constexpr int PS = 4 * kRowsDig;
+      const int ta = min(T.ct, gs * GW * T.tpg), tb = min(T.ct, (gs * GW + GW) * T.tpg);
+      auto group_end = [&](int g, double m, double v) {
+        if (shares == 1) f64_fold(Mt, St, m, v, fast);
+        else if (h == 0) part[g * PS] = make_double2(m, v);
+      };
+      if (!any) {
+        // no such row tile
+      } else if (fast) {
+        f16x8 y0[NC], y1[NC];
+        double gsum = 0.0, srun = 0.0;
+        int g = gs * GW;
+        int gend = min(T.ct, ta + T.tpg), send = min(gend, ta + T.tps);
+        auto tile = [&](const f16x8 (&yt)[NC], int t) {
+          srun += (double)dig_tile<D>(yt, x);
+          if (t + 1 == send) {
+            gsum += srun;
+            srun = 0.0;
+            if (send == gend) {
+              group_end(g, 0.0, gsum);
+              gsum = 0.0;
+              ++g;
+              gend = min(T.ct, gend + T.tpg);
+            }
+            send = min(gend, send + T.tps);
+          }
+        };
+        if (ta < tb) cols.load(ta, y0);
+#pragma unroll 1
+        for (int t = ta; t < tb; t += 2) {
+          cols.load(min(t + 1, T.ct - 1), y1);
+          tile(y0, t);
+          if (t + 1 >= tb) break;
+          cols.load(min(t + 2, T.ct - 1), y0);
+          tile(y1, t + 1);
+        }
+        for (; g < gs * GW + GW; ++g) group_end(g, 0.0, 0.0);   // empty groups
+      } else {
+#pragma unroll 1
+        for (int g = gs * GW; g < gs * GW + GW; ++g) {
+          const int tA = min(T.ct, g * T.tpg), tB = min(T.ct, g * T.tpg + T.tpg);
+          double gm = m0, gv = 0.0;
+#pragma unroll 1
+          for (int t = tA; t < tB; t += T.tps) {
+            double m, v;
+            dig_free_range<D>(cols, x, base, t, min(tB, t + T.tps), h, m, v);
+            f64_fold(gm, gv, m, v, false);
+          }
+          group_end(g, gm, gv);
+        }
+      }
+      if (shares > 1) {   // (every wave is here once: one round of row tiles)
+        __syncthreads();
+        if (gs != 0 || !any) continue;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) f64_fold(Mt, St, part[g * PS].x, part[g * PS].y, fast);
+      }
+      if (Mt == -(double)INFINITY) Mt = 0.0;
+      if (!owner) Mt = St = 0.0;
+      const bool o[1] = {owner}, lv[1] = {owner && live};
+      const double lo[1] = {lse_old}, l2[1] = {lm}, mt[1] = {Mt}, st[1] = {St};
+      const float ww[1] = {w};
+      finish_rows_r<kRowsDig, 1, 1, double, true>(L, P, 0, si, rt, o, lv, fast, M, lo, l2, ww, mt, st,
+                                                  rhat);
+    }
+    __syncthreads();
+    // every wave takes the same turn (the aggregates are complete)
+    if (ph == F_HALF) {
+      ph = G_HALF;
+      if (k > 1 && (k - 1) % R.ae == 0) {
+        rhat = lane_aggregate(agg_f, 0, 0, tx, false).sum;
+        if (!isfinite(rhat) || rhat <= L.tau_screen) ph = CHECK;
+      }
+    } else if (ph == CHECK) {
+      // the decision of finish_rows_r's last item
+      const float rcol = lane_aggregate(agg_c, 0, 0, ty, false).sum;
+      const bool finite = isfinite(rhat) && isfinite(rcol);
+      const bool stop = !finite || fmaxf(rhat, rcol) <= L.tol;
+      if (tid == 0) {
+        atomicAdd(&L.nchk[si.lane], 1);
+        L.audit[s].rhat = rhat;
+        L.audit[s].rcol = rcol;
+        if (isfinite(rhat)) atomicAdd(&L.ctrl->screen_pos, 1);
+        if (stop) retire_lane(L, P, s, si, finite ? 0 : 2, rhat, rcol);
+        else atomicAdd(&L.ctrl->check_fail, 1);
+      }
+      if (stop) {   // the audited state goes out (the emission reads lse)
+        double* const ox = reinterpret_cast<double*>(R.lse[0][pk1]) + (size_t)s * R.pad[0];
+        double* const oy = reinterpret_cast<double*>(R.lse[1][pk1]) + (size_t)s * R.pad[1];
+        for (int i = tid; i < si.n; i += 64 * NW)
+          ox[i] = reinterpret_cast<const double*>(lsx + pk1 * tx * 256)[i];
+        for (int i = tid; i < si.m; i += 64 * NW) oy[i] = reinterpret_cast<const double*>(lsy)[i];
+        return;
+      }
+      ph = G_HALF;
+    } else {
+      if (k == R.k1) break;
+      ++k;
+      ph = F_HALF;
+    }
+  }
+  // the state of cycle k1 goes out
+  const int par = R.k1 & 1;
+  for (int side = 0; side < 2; ++side) {
+    const size_t p0 = (size_t)s * R.pad[side];
+    double* const lse = reinterpret_cast<double*>(R.lse[side][par]) + p0;
+    f16x4* const gam = reinterpret_cast<f16x4*>(reinterpret_cast<double*>(R.gam[side][par]) + p0);
+    const double* const ls = reinterpret_cast<const double*>(side ? lsy : lsx + par * tx * 256);
+    const f16x4* const op = reinterpret_cast<const f16x4*>(side ? opy : opx + par * tx * 256);
+    for (int i = tid; i < (side ? si.m : si.n); i += 64 * NW) {
+      lse[i] = ls[i];
+      gam[i] = op[i];
+    }
+  }
+  for (int q = tid; q < ty; q += 64 * NW) R.agg_g[(size_t)s * L.abmax + q] = agg_g[q];
 }
 
 // ----------------------------------------------- materialised-cost half-steps
@@ -3696,6 +4019,16 @@ static hipError_t launch_dig_d(const Launch& a, int variant, int blocks, hipStre
   return hipGetLastError();
 }
 
+template <int D>
+static hipError_t launch_resident_d(const Launch& a, const ResidentArgs& r, int A, size_t lds,
+                                    hipStream_t st) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resident<D>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResidentLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_resident<D>), dim3(A), dim3(64 * kResidentWaves), lds, st, a, r);
+  return hipGetLastError();
+}
+
 }  // namespace ds
 
 // Entry points used by the host runtime (C++ linkage, same library).
@@ -3805,6 +4138,52 @@ hipError_t launch_update_dig(const Launch& a, int d, int variant, int blocks, hi
     case 14: return launch_dig_d<14>(a, variant, blocks, st, e0, e1);
     case 15: return launch_dig_d<15>(a, variant, blocks, st, e0, e1);
     case 16: return launch_dig_d<16>(a, variant, blocks, st, e0, e1);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+size_t resident_lds_bytes(int d, int n, int m) {
+  switch (d) {
+    case 1: return resident_lds<1>(n, m);
+    case 2: return resident_lds<2>(n, m);
+    case 3: return resident_lds<3>(n, m);
+    case 4: return resident_lds<4>(n, m);
+    case 5: return resident_lds<5>(n, m);
+    case 6: return resident_lds<6>(n, m);
+    case 7: return resident_lds<7>(n, m);
+    case 8: return resident_lds<8>(n, m);
+    case 9: return resident_lds<9>(n, m);
+    case 10: return resident_lds<10>(n, m);
+    case 11: return resident_lds<11>(n, m);
+    case 12: return resident_lds<12>(n, m);
+    case 13: return resident_lds<13>(n, m);
+    case 14: return resident_lds<14>(n, m);
+    case 15: return resident_lds<15>(n, m);
+    case 16: return resident_lds<16>(n, m);
+    default: return ~(size_t)0;
+  }
+}
+hipError_t launch_resident(const Launch& a, const ResidentArgs& r, int d, int A, size_t lds,
+                           hipStream_t st) {
+  if (A <= 0) return hipSuccess;
+  if (lds == 0 || lds > kResidentLds) return hipErrorInvalidValue;
+  switch (d) {
+    case 1: return launch_resident_d<1>(a, r, A, lds, st);
+    case 2: return launch_resident_d<2>(a, r, A, lds, st);
+    case 3: return launch_resident_d<3>(a, r, A, lds, st);
+    case 4: return launch_resident_d<4>(a, r, A, lds, st);
+    case 5: return launch_resident_d<5>(a, r, A, lds, st);
+    case 6: return launch_resident_d<6>(a, r, A, lds, st);
+    case 7: return launch_resident_d<7>(a, r, A, lds, st);
+    case 8: return launch_resident_d<8>(a, r, A, lds, st);
+    case 9: return launch_resident_d<9>(a, r, A, lds, st);
+    case 10: return launch_resident_d<10>(a, r, A, lds, st);
+    case 11: return launch_resident_d<11>(a, r, A, lds, st);
+    case 12: return launch_resident_d<12>(a, r, A, lds, st);
+    case 13: return launch_resident_d<13>(a, r, A, lds, st);
+    case 14: return launch_resident_d<14>(a, r, A, lds, st);
+    case 15: return launch_resident_d<15>(a, r, A, lds, st);
+    case 16: return launch_resident_d<16>(a, r, A, lds, st);
     default: return hipErrorInvalidValue;
   }
 }

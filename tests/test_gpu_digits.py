@@ -117,3 +117,35 @@ def test_lanes_out_of_range_keep_the_vector_kernels(ragged):
     # retirement in such a window: every lane stops where the oracle stops
     got = run_gpu(w, 1e-2, max_iter=400)
     compare(w, got, run_oracle(w, 1e-2, max_iter=400), 1e-2, max_iter=400)
+
+
+@pytest.mark.parametrize("d,n,m", [(2, 64, 64), (3, 20, 150), (3, 300, 90), (5, 129, 33), (7, 97, 260),
+                                   (8, 64, 200), (16, 160, 65), (1, 1, 40)])
+def test_resident_lanes_against_the_launches(d, n, m):
+    # small lanes run many cycles per launch, a block each (k_resident); shadow
+    # replay runs the same window through the per-half launches: the same bits, and
+    # the oracle's decisions (row tiles shared by 8, 4, 2 and 1 waves; one row)
+    for ragged in (False, True):
+        w = _window(6, n, m, d, seed=21, ragged=ragged)
+        log(f"[case] resident d={d} n={n} m={m} ragged={ragged}")
+        for tol, max_iter, ae in ((1e-3, 300, 1), (1e-3, 37, 4), (1e-9, 18, 1)):
+            kw = dict(max_iter=max_iter, audit_every=ae)
+            got, ref = run_gpu(w, tol, **kw), run_gpu(w, tol, flags=1, **kw)   # DS_F_SHADOW
+            for k in ("f", "g", "depth", "status", "order"):
+                assert np.array_equal(got[k], ref[k]), (tol, k)
+            assert np.array_equal(got["residual"], ref["residual"])
+        compare(w, run_gpu(w, 1e-3, max_iter=300), run_oracle(w, 1e-3, max_iter=300), 1e-3,
+                max_iter=300)
+
+
+def test_resident_slices_and_launches_in_one_solve():
+    # a wide window of 512-point telemetry lanes starts resident and ends, with few
+    # lanes left, in per-half launches; the bits are those of either alone
+    w = wl.make("c3", W=200, n=192, m=192)
+    log("[case] resident handover, 200 telemetry lanes of 192 points")
+    got = run_gpu(w, 1e-3, max_iter=1500, streams=1)
+    ref = run_gpu(w, 1e-3, max_iter=1500, streams=1, flags=1)
+    for k in ("f", "g", "depth", "status", "residual", "order"):
+        assert np.array_equal(got[k], ref[k]), k
+    st = got["stats"]
+    assert st.slots_update == int(got["depth"].sum()) and st.l_max == int(got["depth"].max())
