@@ -72,6 +72,13 @@ bool uses_f64(const ds_problem* pr, const ds_options* op) {
   return pr->d <= ds::kMaxDF64;
 }
 
+// The materialised cost read once per cycle: by the window's padded shape alone, so
+// that a lane's bits depend neither on the width nor on what is left of it.
+bool mat_onepass(const ds_problem* pr, const ds_options* op) {
+  return uses_mat(pr, op) && pr->n_max >= ds::kMatCyclePts && pr->m_max >= ds::kMatCyclePts &&
+         (long long)pr->n_max * pr->m_max >= ds::kMatCycleTerms;
+}
+
 struct Carver {
   char* base;
   size_t off = 0;
@@ -140,6 +147,7 @@ ds::Layout plan(const ds_problem* pr, const ds_options* op, void* ws) {
   L.ctrl = c.take<ds::Ctrl>(1);
   L.Q = L.mat ? c.take<float>(W * (size_t)L.pad[0] * (size_t)L.pad[1]) : nullptr;
   L.QT = L.mat ? c.take<float>(W * (size_t)L.pad[0] * (size_t)L.pad[1]) : nullptr;
+  if (mat_onepass(pr, op)) L.cpart = c.take<float2>(W * (size_t)L.rbmax * (size_t)L.pad[1]);
   L.guard = (op->flags & DS_F_GUARD) ? 1 : 0;
   for (int side = 0; side < 2; ++side) {
     L.agg64[side] = L.guard ? c.take<double2>(W * (size_t)L.rbmax) : nullptr;
@@ -466,6 +474,7 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     l.Q = L.Q; l.QT = L.QT; l.q_lane = (size_t)L.pad[0] * L.pad[1]; l.q_ld = L.pad[1];
     l.qt_ld = L.pad[0];
     l.spart = L.spart; l.kpart = L.kpart; l.scnt = L.scnt; l.nslots = L.nslots;
+    l.cpart = L.cpart;
     return l;
   };
   // DS_F_TIMING: both launches of every kSampleEvery-th cycle (and the final
@@ -521,25 +530,34 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
   // lanes 38.3 / 27.5 / 42.1, 256 lanes 154 / 106 / 82. Eight shares of the
   // columns pay for long sweeps of few rows: one LiDAR lane of 4096 points 23.5
   // against 26.5 with four, one mixture lane of 1024 points 17.5 against 16.9.
+  // Long sweeps (eight tiles per group or more) make little of a block's fixed
+  // costs and gain from even shares: there the finer layouts run one and a half and
+  // three rounds (70 LiDAR lanes of up to 700 x 6000 points 58 against 68 us per
+  // cycle, 128 of 4096 x 4096 still 667).
   auto pick_dig = [&](int items, int role) -> int {
     const int room = 256 * dig_waves_per_simd(d);
     const int tiles = items * parts;
     if (tiles <= 64 && tpg[role] >= 8) return DIG_1X8;
-    if (4 * tiles <= room) return DIG_1X4;
-    if (2 * tiles <= room) return DIG_2X2;
+    const bool deep = tpg[role] >= 8;
+    if (4 * tiles <= (deep ? room + room / 2 : room)) return DIG_1X4;
+    if (2 * tiles <= (deep ? 3 * room : room)) return DIG_2X2;
     return DIG_4X1;
   };
   auto blocks_of = [&](int items) -> int { return std::max(items, 0); };
   int seqno = 0;   // update launches issued (see HostSnap::progress)
   auto run = [&](Launch l, int variant, int vdig, int blocks, bool sample, int cycle,
-                 int kind) -> ds_err {
+                 int kind, int cycle_part = 0) -> ds_err {
+    // cycle_part (materialised cost read once per cycle): 1 the pass over the
+    // cost, 2 the columns' finish
     l.seqno = ++seqno;
     const bool timed = tm.on && sample && (int)timed_launches.size() < kMaxTimed;
     // the events are part of the kernel's own dispatch: they time the kernel,
     // not the queue around it
     const int e0 = timed ? tm.take() : -1, e1 = timed ? tm.take() : -1;
     hipEvent_t h0 = e0 >= 0 ? (*tm.pool)[e0] : nullptr, h1 = e1 >= 0 ? (*tm.pool)[e1] : nullptr;
-    if (mat) HIP_TRY(launch_update_mat(l, blocks, st, h0, h1));
+    if (cycle_part == 1) HIP_TRY(launch_mat_cycle(l, blocks, st, h0, h1));
+    else if (cycle_part == 2) HIP_TRY(launch_mat_cols(l, blocks, st, h0, h1));
+    else if (mat) HIP_TRY(launch_update_mat(l, blocks, st, h0, h1));
     else if (precise) {
       // each kernel takes the items of its own lanes; a window almost always
       // holds one kind only. The events of a timed launch go to the first.
@@ -572,23 +590,30 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
                              (int64_t)(sizeof(SlotInfo) + sizeof(Decision));
   // Small lanes: slices of many cycles in one launch, a block per lane
   // (k_resident), as long as that is the faster way to run the lanes that are
-  // left. Per cycle a resident lane takes res_fix plus its 32 x 32 tiles on one
-  // CU; the per-half launches take a fixed time plus all lanes' tiles over the
-  // chip. Both leave the same state, so the choice is taken anew at every slice.
+  // left. Per cycle a resident lane takes a fixed time plus the 32 x 32 tiles and
+  // row tiles of its busiest wave; the per-half launches take a fixed time plus all
+  // lanes' tiles over the chip. Both leave the same state, so the choice is taken
+  // anew at every slice.
   const bool may_reside = active && precise && n_dig == W && !shadow && !guard && !tm.on;
   size_t lds_top = 0;   // (of every lane's own shape: a small one may take more than a larger one)
-  double tiles_top = 0.0, tiles_sum = 0.0;
+  double reside_top = 0.0, tiles_sum = 0.0;
   for (int t = 0; t < W; ++t) {
-    const double tl = (double)((lanes[t].n + 31) / 32) * (double)((lanes[t].m + 31) / 32);
+    const int tx = (lanes[t].n + 31) / 32, ty = (lanes[t].m + 31) / 32;
     if (may_reside) lds_top = std::max(lds_top, resident_lds_bytes(d, lanes[t].n, lanes[t].m));
-    tiles_top = std::max(tiles_top, tl);
-    tiles_sum += tl;
+    double us = kResidentFixUs;
+    for (int half = 0; half < 2; ++half) {
+      const int rt = half ? ty : tx, ct = half ? tx : ty;
+      const int turns = (rt + 7) / 8;   // row tiles of a wave; up to four are shared by all
+      us += turns * kResidentRowUs + (rt >= 5 ? (double)turns * ct : rt * ct / 8.0) * resident_tile_us(d);
+    }
+    reside_top = std::max(reside_top, us);
+    tiles_sum += (double)tx * (double)ty;
   }
   const bool reside_fits = may_reside && lds_top <= kResidentLds;
   // us per cycle of `A` lanes of this sub-batch (the others like it)
   auto reside_us = [&](int A) -> double {
     const int rounds = (A * parts + 255) / 256;
-    return rounds * (kResidentFixUs + 2.0 * tiles_top * resident_tile_us(d));
+    return rounds * reside_top;
   };
   auto launches_us = [&](int A) -> double {
     return kLaunchesFixUs + 2.0 * tiles_sum / W * A * parts * launches_tile_us(d) / 256.0;
@@ -691,8 +716,10 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     // guarded release: the export rounding of state k-1's f, before its check
     if (audit_prev && guard) lf.p[0].gerr_out = L.gerr[0];
     const int vf = pick(items[0], 0);
+    // materialised cost: both halves' sums from one read of it
+    const bool onepass = L.cpart != nullptr;
     lf.nb0 = blocks_of(items[0]);
-    ds_err r = run(lf, vf, pick_dig(items[0], 0), lf.nb0, sample, k, 0);
+    ds_err r = run(lf, vf, pick_dig(items[0], 0), lf.nb0, sample, k, 0, onepass ? 1 : 0);
     if (r != DS_OK) return r;
     if (audit_prev && guard) {
       // guarded release: float64 verification of state k-1 (the potentials the
@@ -724,11 +751,22 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     // g-half of cycle k (+ column check and decision for state k-1)
     // (the check blocks come last: most of them exit at once, and at the front
     // they would delay the update blocks' dispatch)
+    if (onepass && audit_prev && !guard) {
+      // (the g-half's launch has no sweep to ride on: a launch of its own)
+      Launch lk = make_launch();
+      lk.p[0] = make_pass(1, 1, pk1, pk1, pk1);
+      lk.p[0].decide = 1;
+      lk.p[0].verify_all = shadow ? 1 : 0;
+      lk.p[0].depth = k - 1;
+      lk.nb0 = blocks_of(items[1]);
+      r = run(lk, VAR_MEDIUM, DIG_4X1, lk.nb0, false, k, 1);
+      if (r != DS_OK) return r;
+    }
     Launch lg = make_launch();
     const int vg = pick(items[1], 1);
     const int nbg = blocks_of(items[1]);
     int blocks = nbg;
-    if (audit_prev && !guard) {
+    if (audit_prev && !guard && !onepass) {
       lg.p[0] = make_pass(1, 0, pk1, pk, pk);     // g-half of cycle k
       lg.p[1] = make_pass(1, 1, pk1, pk1, pk1);   // column marginal of state k-1
       lg.p[1].decide = 1;
@@ -742,7 +780,7 @@ ds_err solve_part(const ds_problem* pr, const ds_options* op, const ds_result* r
     }
     // guarded release: the export rounding of state k's g, for its audit
     if (guard && k % ae == 0) lg.p[0].gerr_out = L.gerr[1];
-    r = run(lg, vg, pick_dig(items[1], 1), blocks, sample, k, 0);
+    r = run(lg, vg, pick_dig(items[1], 1), blocks, sample, k, 0, onepass ? 2 : 0);
     if (r != DS_OK) return r;
     launched = k;
   }

@@ -67,6 +67,13 @@ constexpr int kVerifyBlocks = 2048;
 constexpr int kMaxW = 4096;
 constexpr int kMaxDSmall = 32;   // matrix-free kernels
 constexpr int kMaxDF64 = 16;     // matrix-free float64-state kernels
+// Materialised cost: a cycle reads the cost once (k_mat_cycle) in windows of this
+// many terms per lane and more, each side with enough points to fill its blocks.
+// Measured us per cycle, one pass against two half-steps: 2048 x 2048 points 36 / 31
+// at one lane and 41 / 50 at eight; 4096 x 4096 49 / 50 at one, 61 / 104 at four, 238
+// / 376 at sixteen; 8192 x 8192 100 / 122 at one, 234 / 416 at four.
+constexpr long long kMatCycleTerms = 12LL << 20;
+constexpr int kMatCyclePts = 1024;
 constexpr int kMatMaxPts = 16384; // materialised cost: points per lane side (LDS staging, 64 KB)
 constexpr float kFastRange = 64.f;  // max spread of the bound (log2 units) for anchored sums
 // The same for the float64 state: there the anchored exponent (at most this
@@ -215,6 +222,7 @@ struct Layout {
   Ctrl* ctrl;
   float* Q;          // materialised cost [W][pad0][pad1] by caller lane, base-2 units
   float* QT;         // its transpose [W][pad1][pad0]
+  float2* cpart;     // column partials of cycles that read the cost once (else null)
   double2* agg64[2]; // guarded checks: per row block float64 partials [W][rbmax] (else null)
   float4* gerr[2];   // guarded release, float64 state: per caller lane and row block
                      // [W][rbmax] {sum of mass x export rounding, max export rounding,
@@ -306,6 +314,8 @@ struct Launch {
   double2* spart;                 // split float64 launch: group partials
                                   // [nslots][kGroups][rows]
   float2* kpart;                  // matrix-free large d: group partials [nslots][kGroups][rows]
+  float2* cpart;                  // materialised cost, one pass per cycle: column partials of
+                                  // the g-half [W][rbmax][q_ld] (else null)
   int* scnt;                      // and per item its arrival word [nslots], zero between launches
   int nslots;                     // items a launch of either kind may hold (both passes)
 };
@@ -419,15 +429,15 @@ hipError_t launch_update_mfma_k(const Launch& a, int blocks, hipStream_t st,
 // LDS a resident lane may use (a CU's), and what a lane of n x m points takes
 constexpr size_t kResidentLds = 163840;
 size_t resident_lds_bytes(int d, int n, int m);
-// The choice between resident slices and per-half launches (see solve_part): us
-// per cycle, fixed and per 32 x 32 tile of both halves. Measured: a resident lane of
-// 2 x 2 tiles (toy, d = 2) 7.0 us per cycle against 13, of 16 x 16 tiles 37 us at
-// d = 8 and 44 at d = 16 on up to 256 lanes; per-half launches 13 to 14 us for a few
-// lanes, 28 / 48 / 76 us for 64 / 128 / 256 telemetry lanes (d = 16, 16 x 16
-// tiles), 39 us for 64 mixture lanes (d = 8, 32 x 32), 323 us for 64 LiDAR lanes
-// (d = 3, 128 x 128)
-constexpr double kResidentFixUs = 7.0;
-constexpr double resident_tile_us(int d) { return d <= 4 ? 0.045 : d <= 8 ? 0.058 : 0.072; }
+// The choice between resident slices and per-half launches (see solve_part), us per
+// cycle: fixed, per row tile and per 32 x 32 tile of a wave (resident); fixed and per
+// tile over the chip (launches). Measured: a resident lane of 64 x 64 points (d = 2)
+// 7.0 against 13.1, 128 x 128 7.7 to 9.5 against 12 to 17, 200 x 195 11 to 13.5
+// against 12 to 26 (d = 3 to 16, 8 to 250 lanes), 287 x 173 15 to 16.5 against 13 to
+// 17 (14 lanes), 512 x 512 at d = 16 42 against 28 / 48 / 76 (64 / 128 / 256 lanes); 64
+// mixture lanes of 1024 x 1024 39 and 64 LiDAR lanes of 4096 x 4096 323 in launches
+constexpr double kResidentFixUs = 7.0, kResidentRowUs = 0.8;
+constexpr double resident_tile_us(int d) { return d <= 4 ? 0.30 : d <= 8 ? 0.36 : 0.45; }
 constexpr double kLaunchesFixUs = 13.5;
 constexpr double launches_tile_us(int d) {
   return d <= 4 ? 0.036 : d <= 8 ? 0.045 : d <= 12 ? 0.08 : 0.115;
@@ -435,6 +445,12 @@ constexpr double launches_tile_us(int d) {
 // cycles k0..k1 of A lanes, all with digit records, none taking more than `lds` bytes
 hipError_t launch_resident(const Launch& a, const ResidentArgs& r, int d, int A, size_t lds,
                            hipStream_t st);
+// one pass over the materialised cost per cycle: f-half and the g-half's column
+// partials, then the columns' merge and finish
+hipError_t launch_mat_cycle(const Launch& a, int blocks, hipStream_t st, hipEvent_t e0 = nullptr,
+                            hipEvent_t e1 = nullptr);
+hipError_t launch_mat_cols(const Launch& a, int blocks, hipStream_t st, hipEvent_t e0 = nullptr,
+                           hipEvent_t e1 = nullptr);
 hipError_t launch_update_mat(const Launch& a, int blocks, hipStream_t st, hipEvent_t e0 = nullptr,
                              hipEvent_t e1 = nullptr);
 
