@@ -88,7 +88,8 @@ enum {
   DS_F_FORCE_VALU = 4u, /* float32 state on the vector-ALU update kernels (d <= 16) */
   DS_F_FORCE_MFMA = 8u, /* float32 state on the matrix-core update kernels
                            (d <= 32; the default for 16 < d <= 32)             */
-  DS_F_PRECISE = 16u,   /* float64 state and exponent arguments (d <= 16). This
+  DS_F_PRECISE = 16u,   /* float64 state and exponent arguments (d <= 16; each
+                           exponent within 2^-30 before its one rounding). This
                            is the default for d <= 16 unless DS_F_FAST32 or a
                            FORCE flag is given; the flag is kept so a caller can
                            require it (an error where it is unavailable). The
@@ -97,7 +98,9 @@ enum {
                            transpose once per call in the workspace and stream
                            them from HBM by rows in every half-step; the default
                            for d > 32 when n_max, m_max <= 16384 (required here;
-                           2 W n_pad m_pad 4 bytes of workspace)                 */
+                           2 W n_pad m_pad 4 bytes of workspace). Lanes of 12M
+                           terms and more read it once per cycle (column partials
+                           of 1/32 of the cost added to the workspace)            */
   DS_F_GUARD = 64u,     /* guarded release (eq:release-contract in float64): the
                            release is decided on a float64 evaluation of both
                            marginals of exactly the float32 potentials the caller
