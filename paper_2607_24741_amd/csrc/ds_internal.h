@@ -46,10 +46,11 @@ constexpr int kGroups = 8;       // fixed column groups of a lane (whole tiles e
 // wave of its own (k_update_f64_split, one block per group) with the same bits.
 constexpr int kSubGroups = 4;
 // most work items of one pass of a split launch, and of the whole launch (its
-// partials in the workspace hold that many: 224 items with a check pass beside
-// the update, the full 256 without)
+// partials in the workspace hold that many: 192 items with a check pass beside
+// the update, the full 256 without; less than two full passes, so that no window
+// needs more workspace than before its aggregates took 32 rows each)
 constexpr int kSplitItems = 256;
-constexpr int kSplitSlots = 448;
+constexpr int kSplitSlots = 384;
 constexpr int kRowsMfma = 32;    // rows per work item, matrix-core kernel
 constexpr int kRowsValu = 64;    // rows per work item, vector-ALU kernel
 constexpr int kRowsDig = 32;     // rows of a digit tile; the aggregates' unit, float64 state
@@ -316,6 +317,7 @@ struct Launch {
   float2* kpart;                  // matrix-free large d: group partials [nslots][kGroups][rows]
   float2* cpart;                  // materialised cost, one pass per cycle: column partials of
                                   // the g-half [W][rbmax][q_ld] (else null)
+  const float* lse_col;           // its f-half launches: the column side's lse of the input state
   int* scnt;                      // and per item its arrival word [nslots], zero between launches
   int nslots;                     // items a launch of either kind may hold (both passes)
 };

@@ -3018,11 +3018,17 @@ __global__ __launch_bounds__(NT, 2) void k_mat_cycle(Launch L) {
   const int nc4 = (ncols + 3) & ~3;
   const float* gcol = P.gam_col + (size_t)s * P.padc;
   const f32x4 none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  f32x4 gy[CPT], mj[CPT], sj[CPT];
+  // column sums are anchored at the columns' old lse, as the half-steps' are: without
+  // it the terms round at the potentials' size (six times the error over a solve)
+  const float* lcol = L.lse_col + (size_t)s * P.padc;
+  f32x4 gy[CPT], by[CPT], mj[CPT], sj[CPT];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
     const int j = 4 * (tid + NT * c);
     gy[c] = j < nc4 ? *reinterpret_cast<const f32x4*>(gcol + j) : none;   // (padding is -inf)
+    by[c] = j < nc4 ? *reinterpret_cast<const f32x4*>(lcol + j) : none;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) by[c][e] = fabsf(by[c][e]) < INFINITY ? -by[c][e] : 0.f;
     mj[c] = none;
     sj[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -3125,14 +3131,14 @@ __global__ __launch_bounds__(NT, 2) void k_mat_cycle(Launch L) {
     for (int c = 0; c < CPT; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float mx = gam[0] - q[0][c][e];
+        float mx = (gam[0] + by[c][e]) - q[0][c][e];
 #pragma unroll
-        for (int r = 1; r < RG; ++r) mx = fmaxf(mx, gam[r] - q[r][c][e]);
+        for (int r = 1; r < RG; ++r) mx = fmaxf(mx, (gam[r] + by[c][e]) - q[r][c][e]);
         const float mn = fmaxf(mj[c][e], mx);
         const float ref = mn == -INFINITY ? 0.f : mn;
         float v[RG];
 #pragma unroll
-        for (int r = 0; r < RG; ++r) v[r] = ex2((gam[r] - q[r][c][e]) - ref);
+        for (int r = 0; r < RG; ++r) v[r] = ex2(((gam[r] + by[c][e]) - q[r][c][e]) - ref);
 #pragma unroll
         for (int w = RG / 2; w > 0; w >>= 1)
 #pragma unroll
@@ -3212,7 +3218,7 @@ __global__ __launch_bounds__(256) void k_mat_cols(Launch L) {
   Mt = !owner || Mt == -INFINITY ? 0.f : Mt;
 #pragma unroll
   for (int u = 0; u < 4; ++u) St += sh[u][lane].y * ex2(sh[u][lane].x - Mt);
-  finish_rows<kRowsValu, 1, float>(L, P, s, si, rb, owner, owner && lse_old != INFINITY, false, 0.f,
+  finish_rows<kRowsValu, 1, float>(L, P, s, si, rb, owner, owner && lse_old != INFINITY, true, 0.f,
                                    lse_old, lm, w, Mt, St, NAN);
 }
 
